@@ -62,8 +62,6 @@ caddtree_status_t hip_fail(hipError_t e, const char* what) {
   return fail(CADDTREE_E_HIP, "%s: %s (%d)", what, hipGetErrorString(e), (int)e);
 }
 
-size_t elem_bytes(caddtree_dtype_t d) { return d == CADDTREE_BF16 ? 2 : 4; }
-
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The value a C caller stored in an enum-typed field or argument, read as the int it is: a C
@@ -130,8 +128,6 @@ caddtree_status_t run_reduce(const caddtree_plan* p, const void* logits, int64_t
   const caddtree::ReduceShape sh = caddtree::reduce_default_shape(a.rows, (int32_t)p->V, p->dtype);
   a.waves_per_row = p->k1_waves > 0 ? p->k1_waves : sh.waves;
   a.unroll = p->k1_unroll > 0 ? p->k1_unroll : sh.unroll;
-  const size_t es = elem_bytes(p->dtype);
-  a.aligned = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && ((size_t)row_stride * es) % 16 == 0;
   a.ids = ids;
   a.logit = logit;
   a.lq = lq;

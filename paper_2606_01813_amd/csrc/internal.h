@@ -21,7 +21,6 @@ struct ReduceArgs {
   int32_t K;
   int32_t waves_per_row; // 1 .. 16
   int32_t unroll;        // 16-byte loads in flight per lane: 4 or 8
-  bool aligned;          // rows start on 16-byte boundaries
   int32_t* ids;          // [rows, K]
   float* logit;          // [rows, K]
   float* lq;             // [rows, K] or nullptr

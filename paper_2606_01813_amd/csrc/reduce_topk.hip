@@ -2,9 +2,13 @@
 // LSE = log sum_v exp(l_v) and the top-K tokens by (logit desc, id asc)
 // (Sec. 3.2, eq. marginals; the Require line of Algorithm 1).
 //
-// One HBM pass per row.  A row is cut into `waves_per_row` contiguous
-// segments, one wavefront each, all in one workgroup.  A wavefront streams
-// 16-byte loads (8 bf16 or 4 fp32 per lane, 1 KiB per wave per load) and
+// One HBM pass per row.  The row's 16-byte aligned part is cut into `waves_per_row`
+// contiguous segments, one wavefront each, all in one workgroup; the few elements
+// before and after it (rows of a vocabulary or a stride that is no multiple of 16
+// bytes start anywhere) are one more step of the last wavefront, one element a lane.
+// (Element loads for every row off a 16-byte boundary took 181 us for 48 x 15 rows of
+// 100003 bf16 logits; the vectors and the edge step take 40 us.)
+// A wavefront streams 16-byte loads (8 bf16 or 4 fp32 per lane, 1 KiB per wave per load) and
 // keeps, per lane, an fp64 sum of 2^(x log2 e - r) where r is a wave-uniform
 // integer exponent that only grows: when it moves, the sums are rescaled by an
 // exact power of two.  The exponent argument is formed with a two-part log2 e
@@ -114,10 +118,10 @@ __device__ __forceinline__ void list_insert(WaveState& s, float v, int id, float
   if (kid != INT_MAX) { s.thr = readlane_f(s.lv, K - 1); s.thr_id = kid; }
 }
 
-// Rare path of one chunk: move the reference exponent, then insert candidates.
-// x[j] is element base + lane * VEC + j; valid elements have bit j set in ok.
-template <int VEC>
-__device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], unsigned ok, float cmax, int base, int K) {
+// Rare path of one step: move the reference exponent, then insert candidates.
+// x[j] of lane l is element id_of(l, j) of the row; lanes with ok unset hold none.
+template <int VEC, typename IdOf>
+__device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool ok, float cmax, IdOf id_of, int K) {
   if (__ballot(cmax > s.mx)) {
     const float m = wave_max(cmax);
     s.mx = m;
@@ -129,43 +133,39 @@ __device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], unsign
   }
 #pragma unroll
   for (int j = 0; j < VEC; ++j) {
-    unsigned long long m = __ballot(((ok >> j) & 1u) && x[j] >= s.thr);
+    unsigned long long m = __ballot(ok && x[j] >= s.thr);
     while (m) {
       const int l = __builtin_ctzll(m);
       m &= m - 1;
       const float v = readlane_f(x[j], l);
-      const int id = base + l * VEC + j;
+      const int id = id_of(l, j);
       if (before(v, id, s.thr, s.thr_id)) list_insert(s, v, id, s.r, K);
     }
   }
 }
 
-template <int VEC>
-__device__ __forceinline__ void chunk(WaveState& s, const float (&x)[VEC], unsigned ok, int base, int K) {
-  float cmax = -INFINITY;
-#pragma unroll
-  for (int j = 0; j < VEC; ++j) cmax = ((ok >> j) & 1u) ? fmaxf(cmax, x[j]) : cmax;
-  if (__builtin_expect(__ballot(cmax >= s.thr) != 0, 0)) rare<VEC>(s, x, ok, cmax, base, K);
-#pragma unroll
-  for (int j = 0; j < VEC; ++j) {
-    const float t = term(x[j], s.r);
-    s.acc += ((ok >> j) & 1u) ? (double)t : 0.0;
-  }
+// The elements outside the aligned part: at most one a lane (x; -inf in a lane without one).
+template <typename IdOf>
+__device__ __forceinline__ void edge_step(WaveState& s, float x, bool ok, IdOf id_of, int K) {
+  const float xs[1] = {x};
+  if (__ballot(ok && x >= s.thr) != 0) rare<1>(s, xs, ok, x, id_of, K);
+  s.acc += ok ? (double)term(x, s.r) : 0.0;
 }
 
-// A full chunk.  Every lane adds its terms pairwise in fp32 and the result once in
+// A chunk: one vector a lane, elements base + lane * VEC + j (a lane with ok unset holds -inf, whose
+// terms are zero).  Every lane adds its terms pairwise in fp32 and the result once in
 // fp64.  A lane whose elements include a top-K candidate (the rare path) then adds the
 // fp64 difference between its terms summed one by one and that fp32 sum, so its
 // contribution is the fp64 sum of its fp32 terms and the final fp64 correction of the
 // top-K terms removes their whole error.
 template <int VEC>
-__device__ __forceinline__ void chunk_full(WaveState& s, const float (&x)[VEC], int base, int K) {
+__device__ __forceinline__ void chunk(WaveState& s, const float (&x)[VEC], bool ok, int base, int K) {
   float cmax = x[0];
 #pragma unroll
   for (int j = 1; j < VEC; ++j) cmax = fmaxf(cmax, x[j]);
-  const bool cand = cmax >= s.thr;
+  const bool cand = ok && cmax >= s.thr;
   const bool any = __ballot(cand) != 0;
-  if (__builtin_expect(any, 0)) rare<VEC>(s, x, (1u << VEC) - 1u, cmax, base, K);
+  if (__builtin_expect(any, 0)) rare<VEC>(s, x, ok, cmax, [base](int l, int j) { return base + l * VEC + j; }, K);
   float t[VEC], p[VEC];
 #pragma unroll
   for (int j = 0; j < VEC; ++j) p[j] = t[j] = term(x[j], s.r);
@@ -196,16 +196,11 @@ __device__ __forceinline__ void unpack(const uint4& q, float (&x)[4]) {
 __device__ __forceinline__ float to_f32(float v) { return v; }
 __device__ __forceinline__ float to_f32(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
 
-// guarded element-wise load of one lane's VEC elements starting at element e
-template <typename T, int VEC>
-__device__ __forceinline__ unsigned load_guarded(const T* rowp, int e, int V, float (&x)[VEC]) {
-  unsigned ok = 0;
-#pragma unroll
-  for (int j = 0; j < VEC; ++j) {
-    if (e + j < V) { x[j] = to_f32(rowp[e + j]); ok |= 1u << j; }
-    else x[j] = -INFINITY;
-  }
-  return ok;
+// 16 bytes of -inf elements
+template <typename T>
+__device__ __forceinline__ uint4 neg_inf_vec() {
+  const uint32_t w = sizeof(T) == 2 ? 0xFF80FF80u : 0xFF800000u;
+  return make_uint4(w, w, w, w);
 }
 
 // (value, id) as one unsigned 64-bit key whose order is the top-K order: the value's bits mapped
@@ -220,7 +215,7 @@ __device__ __forceinline__ uint64_t order_key(float v, int id) {
 __device__ __forceinline__ int key_id(uint64_t k) { return INT_MAX - (int)(uint32_t)k; }
 
 // kUnroll: 16-byte loads in flight per lane (4 or 8); kS: wavefronts per row (1 .. 16)
-template <typename T, bool kAligned, int kUnroll, int kS>
+template <typename T, int kUnroll, int kS>
 __global__ void __launch_bounds__(1024)
 reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int K,
                    int32_t* __restrict__ out_ids, float* __restrict__ out_logit,
@@ -242,8 +237,13 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   constexpr int S = kS;
   const int64_t row = blockIdx.x;
   const T* rowp = logits + row * row_stride;
-  const int nch = (V + CH - 1) / CH;
-  const int nfull = V / CH;
+  // the row's aligned part: nv vectors from element `head` on
+  const int mis = (int)((reinterpret_cast<uintptr_t>(rowp) & 15u) / sizeof(T));
+  const int head = mis == 0 ? 0 : (VEC - mis < V ? VEC - mis : V);
+  const int nv = (V - head) / VEC;
+  const uint4* pv = reinterpret_cast<const uint4*>(rowp + head);
+  const int nch = (nv + kWave - 1) / kWave;
+  const int nfull = nv / kWave;
   const int c0 = (int)((int64_t)wave * nch / S);
   const int c1 = (int)((int64_t)(wave + 1) * nch / S);
   const int cfull = c1 < nfull ? c1 : nfull;
@@ -253,68 +253,65 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   s.lv = -INFINITY; s.lid = INT_MAX; s.lr = 0.f;
 
   int c = c0;
-  if (kAligned) {
-    const uint4* p4 = reinterpret_cast<const uint4*>(rowp);
-    if (c + kUnroll <= cfull) {
-      const uint4* lp = p4 + lane + (int64_t)c * (CH / VEC);   // chunk c of this lane
-      uint4 q[kUnroll];
+  if (c + kUnroll <= cfull) {
+    const uint4* lp = pv + lane + (int64_t)c * kWave;   // chunk c of this lane
+    uint4 q[kUnroll];
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) q[u] = stream_load(lp + u * (CH / VEC));
-      // the first group sets the reference exponent and the initial threshold
-      float g = -INFINITY;
+    for (int u = 0; u < kUnroll; ++u) q[u] = stream_load(lp + u * kWave);
+    // the first group sets the reference exponent and the initial threshold
+    float g = -INFINITY;
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {   // unpacked twice: keeps the live registers to one chunk
-        float x[VEC];
-        unpack(q[u], x);
+    for (int u = 0; u < kUnroll; ++u) {   // unpacked twice: keeps the live registers to one chunk
+      float x[VEC];
+      unpack(q[u], x);
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) g = fmaxf(g, x[j]);
-      }
-      s.mx = wave_max(g);
-      s.r = ceilf(s.mx * kLog2eHi);
-      int kp = 1;
-      while (kp < K) kp <<= 1;
-      const int grp = kWave / kp;           // lanes per group; kp groups
-      float gm = g;
-      for (int o = 1; o < grp; o <<= 1) gm = fmaxf(gm, __shfl_xor(gm, o));
-      for (int o = grp; o < kWave; o <<= 1) gm = fminf(gm, __shfl_xor(gm, o));
-      s.thr = gm;
-      // a ring of kUnroll loads in flight: each chunk's slot (the first group's too) is refilled with the
-      // load kUnroll chunks ahead as soon as its registers are unpacked, before its arithmetic
-      for (; c + 2 * kUnroll <= cfull; c += kUnroll) {
-        lp += kUnroll * (CH / VEC);
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          float x[VEC];
-          unpack(q[u], x);
-          q[u] = stream_load(lp + u * (CH / VEC));
-          chunk_full<VEC>(s, x, (c + u) * CH, K);
-        }
-      }
+      for (int j = 0; j < VEC; ++j) g = fmaxf(g, x[j]);
+    }
+    s.mx = wave_max(g);
+    s.r = ceilf(s.mx * kLog2eHi);
+    int kp = 1;
+    while (kp < K) kp <<= 1;
+    const int grp = kWave / kp;           // lanes per group; kp groups
+    float gm = g;
+    for (int o = 1; o < grp; o <<= 1) gm = fmaxf(gm, __shfl_xor(gm, o));
+    for (int o = grp; o < kWave; o <<= 1) gm = fminf(gm, __shfl_xor(gm, o));
+    s.thr = gm;
+    // a ring of kUnroll loads in flight: each chunk's slot (the first group's too) is refilled with the
+    // load kUnroll chunks ahead as soon as its registers are unpacked, before its arithmetic
+    for (; c + 2 * kUnroll <= cfull; c += kUnroll) {
+      lp += kUnroll * kWave;
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         float x[VEC];
         unpack(q[u], x);
-        chunk_full<VEC>(s, x, (c + u) * CH, K);
+        q[u] = stream_load(lp + u * kWave);
+        chunk<VEC>(s, x, true, head + (c + u) * CH, K);
       }
-      c += kUnroll;
     }
-    for (; c < cfull; ++c) {
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
       float x[VEC];
-      unpack(stream_load(p4 + (c * CH + lane * VEC) / VEC), x);
-      chunk_full<VEC>(s, x, c * CH, K);
+      unpack(q[u], x);
+      chunk<VEC>(s, x, true, head + (c + u) * CH, K);
     }
+    c += kUnroll;
   }
-  for (; c < c1; ++c) {   // unaligned rows, or the ragged last chunk of the row
+  for (; c < c1; ++c) {   // the last chunks; the row's last one may hold fewer than 64 vectors
+    const bool ok = c * kWave + lane < nv;
+    uint4 q = neg_inf_vec<T>();
+    if (ok) q = stream_load(pv + (int64_t)c * kWave + lane);
     float x[VEC];
-    const int e = c * CH + lane * VEC;
-    unsigned ok;
-    if (kAligned && e + VEC <= V) {         // a whole vector of this lane lies in the row
-      unpack(stream_load(reinterpret_cast<const uint4*>(rowp + e)), x);
-      ok = (1u << VEC) - 1u;
-    } else {
-      ok = load_guarded<T, VEC>(rowp, e, V, x);
+    unpack(q, x);
+    chunk<VEC>(s, x, ok, head + c * CH, K);
+  }
+  if (wave == S - 1) {    // elements 0 .. head - 1 and head + nv VEC .. V - 1, fewer than 2 VEC in all
+    const int gap = nv * VEC;
+    const auto id_of = [head, gap](int l, int) { return l < head ? l : gap + l; };
+    const int edge = V - gap;
+    if (edge > 0) {
+      const bool ok = lane < edge;
+      edge_step(s, ok ? to_f32(rowp[id_of(lane, 0)]) : -INFINITY, ok, id_of, K);
     }
-    chunk<VEC>(s, x, ok, c * CH, K);
   }
 
   // wave sum of the per-lane accumulators (fixed order: a DPP scan, the total in the last lane)
@@ -396,28 +393,28 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   if (lane == 0) out_lse[row] = lse;
 }
 
-template <typename T, bool A, int U, int S>
+template <typename T, int U, int S>
 void launch_s(const ReduceArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL((reduce_topk_kernel<T, A, U, S>), dim3((unsigned)a.rows), dim3((unsigned)(kWave * S)), 0, stream,
+  hipLaunchKernelGGL((reduce_topk_kernel<T, U, S>), dim3((unsigned)a.rows), dim3((unsigned)(kWave * S)), 0, stream,
                      static_cast<const T*>(a.logits), a.row_stride, a.V, a.K, a.ids, a.logit, a.lq, a.lse);
 }
 
-template <typename T, bool A, int U>
+template <typename T, int U>
 hipError_t launch_u(const ReduceArgs& a, hipStream_t stream) {
   switch (a.waves_per_row) {
-    case 1: launch_s<T, A, U, 1>(a, stream); break;
-    case 2: launch_s<T, A, U, 2>(a, stream); break;
-    case 4: launch_s<T, A, U, 4>(a, stream); break;
-    case 8: launch_s<T, A, U, 8>(a, stream); break;
-    case 16: launch_s<T, A, U, 16>(a, stream); break;
+    case 1: launch_s<T, U, 1>(a, stream); break;
+    case 2: launch_s<T, U, 2>(a, stream); break;
+    case 4: launch_s<T, U, 4>(a, stream); break;
+    case 8: launch_s<T, U, 8>(a, stream); break;
+    case 16: launch_s<T, U, 16>(a, stream); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-template <typename T, bool A>
+template <typename T>
 hipError_t launch_t(const ReduceArgs& a, hipStream_t stream) {
-  return a.unroll == 8 ? launch_u<T, A, 8>(a, stream) : launch_u<T, A, 4>(a, stream);
+  return a.unroll == 8 ? launch_u<T, 8>(a, stream) : launch_u<T, 4>(a, stream);
 }
 
 }  // namespace
@@ -446,9 +443,7 @@ ReduceShape reduce_default_shape(int64_t rows, int32_t V, caddtree_dtype_t dtype
 
 hipError_t launch_reduce_topk(const ReduceArgs& a, caddtree_dtype_t dtype, hipStream_t stream) {
   if (a.rows == 0) return hipSuccess;
-  if (dtype == CADDTREE_BF16)
-    return a.aligned ? launch_t<uint16_t, true>(a, stream) : launch_t<uint16_t, false>(a, stream);
-  return a.aligned ? launch_t<float, true>(a, stream) : launch_t<float, false>(a, stream);
+  return dtype == CADDTREE_BF16 ? launch_t<uint16_t>(a, stream) : launch_t<float>(a, stream);
 }
 
 }  // namespace caddtree

@@ -1009,3 +1009,38 @@ def test_k1_launch_shapes(waves, unroll, monkeypatch):
     _parity_batch(cfg, list(range(cfg.B)))
     cfg32 = synth.get_config("c4").replace(V=30011, B=2, L=8)
     _parity_batch(cfg32, list(range(cfg32.B)))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("waves", [1, 4, 16])
+def test_k1_rows_at_any_alignment(dtype, waves, monkeypatch):
+    """Rows that start at every element offset from a 16-byte boundary, of lengths around one vector, one
+    chunk and one group of chunks: the elements before and after the aligned part, and a ragged last chunk."""
+    import oracle
+    import torch
+    monkeypatch.setenv("CADDTREE_K1_WAVES", str(waves))
+    vec = 8 if dtype == "bf16" else 4
+    rng = np.random.default_rng(5)
+    for V in (1, 2, vec - 1, vec, vec + 1, 2 * vec + 1, 64 * vec - 1, 64 * vec, 64 * vec + 3, 8 * 64 * vec + 1,
+              17 * 64 * vec + vec + 1):
+        L, B, K = 2, 2, min(V, 8)
+        x32 = (3.0 * rng.standard_normal((B, L, V))).astype(np.float32)
+        x32[:, :, 0] += 6.0                                  # both ends hold a top token
+        x32[:, :, V - 1] += 5.0
+        xs = synth.bf16_bits_from_f32(x32) if dtype == "bf16" else x32
+        cfg = synth.get_config("c1").replace(V=V, B=B, L=L, K=K, cap=8, dtype=dtype)
+        plan = make_plan(cfg)
+        ref = [oracle.marginals(xs[b], dtype, K) for b in range(B)]
+        for off in range(vec):
+            flat = torch.zeros(off + B * L * V, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32,
+                               device="cuda")
+            logits = flat[off:].view(B, L, V)
+            logits.copy_(torch_logits(cfg, xs))
+            out = plan.new_outputs(B, topk=True)
+            plan.reduce_topk(logits, out.topk_ids, out.topk_logit, out.lse, out.topk_lq)
+            torch.cuda.synchronize()
+            h = host(out)
+            for b in range(B):
+                assert np.array_equal(h["topk_ids"][b], ref[b]["ids"]), (V, off, b)
+                assert np.array_equal(h["topk_logit"][b].astype(np.float64), ref[b]["logit"]), (V, off, b)
+                assert np.abs(h["lse"][b] - ref[b]["lse"]).max() <= 1e-7, (V, off, b)
