@@ -10,7 +10,7 @@
 // 100003 bf16 logits; the vectors and the edge step take 40 us.)
 // A wavefront streams 16-byte loads (8 bf16 or 4 fp32 per lane, 1 KiB per wave per load) and
 // keeps, per lane, an fp64 sum of 2^(x log2 e - r) where r is a wave-uniform
-// integer exponent that only grows: when it moves, the sums are rescaled by an
+// integer exponent, a little below the running maximum's, that only grows: when it moves, the sums are rescaled by an
 // exact power of two.  The exponent argument is formed with a two-part log2 e
 // (two fmas), so the only per-term error is the hardware exp2.
 //
@@ -18,13 +18,12 @@
 // DPP row.  An element is a candidate when it is >= the wave threshold (the
 // K-th slot, or an initial lower bound); the fast path is one compare of the
 // lane's chunk maximum per 8 elements, and the rare path inserts candidates one
-// at a time with a DPP row shift.  The initial bound is the minimum over K'
-// (>= K) disjoint lane groups of the group maximum over the first chunks, which
-// is <= the K-th largest element, so no top-K element is ever filtered out.
+// at a time with a DPP row shift.  The initial bound is the K-th largest of the lanes' maxima over
+// the first chunks of all of the row's wavefronts, which is <= the K-th largest element, so no
+// top-K element is ever filtered out.
 //
-// At the end, wave 0 merges the waves' lists (when their K best fit in one wave, each
-// candidate, as a 64-bit key, is ranked against all of them in one pass), combines the
-// per-wave sums,
+// At the end the waves' lists are merged (each candidate, as a 64-bit key, is ranked
+// against all of them in one pass), and wave 0 combines the per-wave sums
 // and replaces the top-K terms' fp32 exp2 values (recomputed bit-identically
 // from the exponent recorded at insertion) by fp64 values, which removes the
 // error of the largest terms from the normaliser.
@@ -47,9 +46,23 @@ constexpr float kNoExp = -1.0e30f;             // "no reference exponent yet"
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// streaming 16-byte load with the non-temporal hint: each byte of the logits is read once
-__device__ __forceinline__ uint4 stream_load(const uint4* p) {
-  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+// Streaming 16-byte loads of a wavefront's segment, with the non-temporal hint (each byte of the logits is
+// read once).  Buffer loads: the segment's base and the chunk's offset are scalars and the lane's offset never
+// changes, so a load needs no vector address arithmetic, and a load past the segment's end returns zeros
+// without touching memory, so the ring needs no branch or clamp at the end of a segment.
+constexpr int kNonTemporal = 2;                 // the nt bit of a buffer load's cache policy
+struct Segment {
+  const char* base;                             // the next group's first vector (wave-uniform)
+  int64_t left;                                 // bytes from there to the segment's end
+  // the U loads of a group: vector u * kWave + lane
+  __device__ __forceinline__ auto rsrc() const {
+    const int64_t cut = left < 0 ? 0 : (left < (1 << 30) ? left : (1 << 30));   // a group is at most 8 KiB
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (int)cut, 0x00027000);
+  }
+};
+template <typename R>
+__device__ __forceinline__ uint4 stream_load(R rsrc, int lane_off, int off) {
+  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off, off, kNonTemporal);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
@@ -82,6 +95,53 @@ __device__ __forceinline__ float wave_max(float v) {
   return readlane_f(v, kWave - 1);
 }
 
+// ---- the 16 largest of the wave's 64 values, for the initial threshold: each row of 16 lanes is sorted in
+// descending order by a bitonic network, then rows are merged pairwise (the larger of a row and the other
+// row reversed is a bitonic row of the 16 largest of both)
+template <int CTRL>
+__device__ __forceinline__ float dpp_row(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+// the value of lane ^ J, J < 16 (XOR 4 and 8: a permutation of the quad or row, then a half-row mirror)
+template <int J>
+__device__ __forceinline__ float row_xor(float v) {
+  if constexpr (J == 1) return dpp_row<0xB1>(v);
+  else if constexpr (J == 2) return dpp_row<0x4E>(v);
+  else if constexpr (J == 4) return dpp_row<0x141>(dpp_row<0x1B>(v));
+  else return dpp_row<0x141>(dpp_row<0x140>(v));
+}
+// one compare-exchange stage at distance J of blocks of KB lanes (KB = 16: every row descending)
+template <int KB, int J>
+__device__ __forceinline__ float row_stage(float v, int lane) {
+  const float o = row_xor<J>(v);
+  const bool keep_max = ((lane & J) == 0) == ((lane & KB & 15) == 0);
+  return keep_max ? fmaxf(v, o) : fminf(v, o);
+}
+__device__ __forceinline__ float row_merge_sort(float v, int lane) {   // a bitonic row to descending order
+  v = row_stage<16, 8>(v, lane);
+  v = row_stage<16, 4>(v, lane);
+  v = row_stage<16, 2>(v, lane);
+  return row_stage<16, 1>(v, lane);
+}
+__device__ __forceinline__ float row_sort(float v, int lane) {
+  v = row_stage<2, 1>(v, lane);
+  v = row_stage<4, 2>(v, lane);
+  v = row_stage<4, 1>(v, lane);
+  v = row_stage<8, 4>(v, lane);
+  v = row_stage<8, 2>(v, lane);
+  v = row_stage<8, 1>(v, lane);
+  return row_merge_sort(v, lane);
+}
+// the 16 largest of two descending rows, in descending order
+__device__ __forceinline__ float row_merge(float a, float b, int lane) {
+  return row_merge_sort(fmaxf(a, dpp_row<0x140>(b)), lane);
+}
+// the 16 largest of four descending rows (one per 16 lanes), in descending order in every row
+__device__ __forceinline__ float merge_rows(float v, int lane) {
+  v = row_merge(v, __shfl_xor(v, 16), lane);
+  return row_merge(v, __shfl_xor(v, 32), lane);
+}
+
 // (v, id) goes before (w, wid) in the order value desc, id asc
 __device__ __forceinline__ bool before(float v, int id, float w, int wid) {
   return v > w || (v == w && id < wid);
@@ -92,6 +152,13 @@ __device__ __forceinline__ float term(float x, float r) {
   a = fmaf(x, kLog2eLo, a);
   return __builtin_amdgcn_exp2f(a);
 }
+
+// The reference exponent for a running maximum of mx: terms of up to 2^3.  The hardware exp2's error is
+// biased and grows with the size of its argument, so the reference sits a little below the maximum, nearer
+// the terms that make up most of the sum of a flat row.  Normaliser against 64 bits, rms over rows of
+// 151936 bf16 logits: 5.2e-8 at the maximum, 1.8e-8 three below it, 3.4e-8 eight below it (normal logits);
+// 2.7e-8, 1.8e-8 and 2.2e-8 (Gumbel noise with a peak).
+__device__ __forceinline__ float ref_exp(float mx) { return ceilf(mx * kLog2eHi) - 3.0f; }
 
 struct WaveState {
   double acc;     // per lane
@@ -118,37 +185,61 @@ __device__ __forceinline__ void list_insert(WaveState& s, float v, int id, float
   if (kid != INT_MAX) { s.thr = readlane_f(s.lv, K - 1); s.thr_id = kid; }
 }
 
+// x[j] of a per-lane j: a tree of bit selects (a select between array elements would become an indexed
+// access, which registers do not have)
+template <int VEC>
+__device__ __forceinline__ float pick(const float (&x)[VEC], int j) {
+  uint32_t t[VEC];
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) t[i] = __float_as_uint(x[i]);
+#pragma unroll
+  for (int w = 1; w < VEC; w <<= 1) {
+    const uint32_t up = (j & w) ? ~0u : 0u;
+#pragma unroll
+    for (int i = 0; i + w < VEC; i += 2 * w) t[i] = (t[i + w] & up) | (t[i] & ~up);
+  }
+  return __uint_as_float(t[0]);
+}
+
 // Rare path of one step: move the reference exponent, then insert candidates.
 // x[j] of lane l is element id_of(l, j) of the row; lanes with ok unset hold none.
+// The insertion stands in one loop over all (lane, j) candidates and not once per j: this path is
+// inlined into every unrolled chunk, and the code of a row is fetched once per launch, so a short
+// launch pays for its length (one copy per j: 62 KB of code for 16 wavefronts, the size of the
+// instruction cache).
 template <int VEC, typename IdOf>
-__device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool ok, float cmax, IdOf id_of, int K) {
+__device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool ok, float cmax, IdOf id_of, int K,
+                                     int lane) {
   if (__ballot(cmax > s.mx)) {
     const float m = wave_max(cmax);
     s.mx = m;
-    const float nr = ceilf(m * kLog2eHi);
+    const float nr = ref_exp(m);
     if (nr > s.r) {
       s.acc = ldexp(s.acc, (int)fmaxf(s.r - nr, -2000.f));
       s.r = nr;
     }
   }
+  uint32_t cm = 0u;                            // bit j: x[j] is a candidate
 #pragma unroll
-  for (int j = 0; j < VEC; ++j) {
-    unsigned long long m = __ballot(ok && x[j] >= s.thr);
-    while (m) {
-      const int l = __builtin_ctzll(m);
-      m &= m - 1;
-      const float v = readlane_f(x[j], l);
-      const int id = id_of(l, j);
-      if (before(v, id, s.thr, s.thr_id)) list_insert(s, v, id, s.r, K);
-    }
+  for (int j = 0; j < VEC; ++j) cm |= (ok && x[j] >= s.thr) ? 1u << j : 0u;
+  unsigned long long m = __ballot(cm != 0u);
+#pragma unroll 1
+  while (m) {
+    const int l = __builtin_ctzll(m);
+    const int jl = __builtin_ctz(cm | 0x100u);   // this lane's next candidate
+    const float v = readlane_f(pick(x, jl), l);
+    const int id = id_of(l, readlane_i(jl, l));
+    if (lane == l) cm &= cm - 1u;
+    if (before(v, id, s.thr, s.thr_id)) list_insert(s, v, id, s.r, K);
+    m = __ballot(cm != 0u);
   }
 }
 
 // The elements outside the aligned part: at most one a lane (x; -inf in a lane without one).
 template <typename IdOf>
-__device__ __forceinline__ void edge_step(WaveState& s, float x, bool ok, IdOf id_of, int K) {
+__device__ __forceinline__ void edge_step(WaveState& s, float x, bool ok, IdOf id_of, int K, int lane) {
   const float xs[1] = {x};
-  if (__ballot(ok && x >= s.thr) != 0) rare<1>(s, xs, ok, x, id_of, K);
+  if (__ballot(ok && x >= s.thr) != 0) rare<1>(s, xs, ok, x, id_of, K, lane);
   s.acc += ok ? (double)term(x, s.r) : 0.0;
 }
 
@@ -159,13 +250,13 @@ __device__ __forceinline__ void edge_step(WaveState& s, float x, bool ok, IdOf i
 // contribution is the fp64 sum of its fp32 terms and the final fp64 correction of the
 // top-K terms removes their whole error.
 template <int VEC>
-__device__ __forceinline__ void chunk(WaveState& s, const float (&x)[VEC], bool ok, int base, int K) {
+__device__ __forceinline__ void chunk(WaveState& s, const float (&x)[VEC], bool ok, int base, int K, int lane) {
   float cmax = x[0];
 #pragma unroll
   for (int j = 1; j < VEC; ++j) cmax = fmaxf(cmax, x[j]);
   const bool cand = ok && cmax >= s.thr;
   const bool any = __ballot(cand) != 0;
-  if (__builtin_expect(any, 0)) rare<VEC>(s, x, ok, cmax, [base](int l, int j) { return base + l * VEC + j; }, K);
+  if (__builtin_expect(any, 0)) rare<VEC>(s, x, ok, cmax, [base](int l, int j) { return base + l * VEC + j; }, K, lane);
   float t[VEC], p[VEC];
 #pragma unroll
   for (int j = 0; j < VEC; ++j) p[j] = t[j] = term(x[j], s.r);
@@ -193,15 +284,8 @@ __device__ __forceinline__ void unpack(const uint4& q, float (&x)[4]) {
   x[2] = __uint_as_float(q.z); x[3] = __uint_as_float(q.w);
 }
 
-__device__ __forceinline__ float to_f32(float v) { return v; }
-__device__ __forceinline__ float to_f32(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
-
-// 16 bytes of -inf elements
-template <typename T>
-__device__ __forceinline__ uint4 neg_inf_vec() {
-  const uint32_t w = sizeof(T) == 2 ? 0xFF80FF80u : 0xFF800000u;
-  return make_uint4(w, w, w, w);
-}
+__device__ __forceinline__ uint32_t raw_bits(const float* p) { return __float_as_uint(*p); }
+__device__ __forceinline__ uint32_t raw_bits(const uint16_t* p) { return *p; }
 
 // (value, id) as one unsigned 64-bit key whose order is the top-K order: the value's bits mapped
 // to an unsigned integer that grows with the value (-0 taken as +0, which compares equal to it),
@@ -222,18 +306,16 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
                    float* __restrict__ out_lq, double* __restrict__ out_lse) {
   constexpr int VEC = Vec<T>::n;
   constexpr int CH = kWave * VEC;
-  __shared__ double s_acc[16];
-  __shared__ float s_r[16];
-  __shared__ float s_lv[16][16];
-  __shared__ int s_lid[16][16];
-  __shared__ float s_lr[16][16];
-  __shared__ uint64_t s_key[kWave];     // the waves' K best as keys, wave w's at w K .. w K + K - 1
-  __shared__ float s_kv[kWave];         // ... their values as read (the sign of a zero included)
-  __shared__ float s_kr[kWave];
+  __shared__ float s_top[16 * kS];      // the waves' 16 largest lane maxima of the first group
+  __shared__ double s_acc[kS];
+  __shared__ float s_r[kS];
+  __shared__ uint64_t s_key[16 * kS];   // the waves' K best as keys
+  __shared__ float s_kv[16 * kS];       // ... their values as read (the sign of a zero included)
+  __shared__ float s_kr[16 * kS];       // ... and the reference exponents at their insertion
   __shared__ int s_sel[16];
 
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
   constexpr int S = kS;
   const int64_t row = blockIdx.x;
   const T* rowp = logits + row * row_stride;
@@ -241,134 +323,142 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   const int mis = (int)((reinterpret_cast<uintptr_t>(rowp) & 15u) / sizeof(T));
   const int head = mis == 0 ? 0 : (VEC - mis < V ? VEC - mis : V);
   const int nv = (V - head) / VEC;
-  const uint4* pv = reinterpret_cast<const uint4*>(rowp + head);
   const int nch = (nv + kWave - 1) / kWave;
-  const int nfull = nv / kWave;
   const int c0 = (int)((int64_t)wave * nch / S);
   const int c1 = (int)((int64_t)(wave + 1) * nch / S);
-  const int cfull = c1 < nfull ? c1 : nfull;
+  const int v1 = c1 * kWave < nv ? c1 * kWave : nv;   // the segment's vectors are c0 kWave .. v1 - 1
 
   WaveState s;
   s.acc = 0.0; s.r = kNoExp; s.mx = -INFINITY; s.thr = -INFINITY; s.thr_id = INT_MAX;
   s.lv = -INFINITY; s.lid = INT_MAX; s.lr = 0.f;
 
+  // elements 0 .. head - 1 and head + nv VEC .. V - 1, fewer than 2 VEC in all: a step of the last
+  // wavefront, loaded ahead of its stream
+  const int gap = nv * VEC;
+  const auto edge_id = [head, gap](int l, int) { return l < head ? l : gap + l; };
+  const int edge = wave == S - 1 ? V - gap : 0;
+  uint32_t edge_raw = 0u;
+  if (lane < edge) edge_raw = raw_bits(rowp + edge_id(lane, 0));
+
+  const int lane_off = lane * 16;
+  Segment seg{reinterpret_cast<const char*>(rowp + head) + (int64_t)c0 * (kWave * 16),
+              (int64_t)(v1 - c0 * kWave) * 16};
   int c = c0;
-  if (c + kUnroll <= cfull) {
-    const uint4* lp = pv + lane + (int64_t)c * kWave;   // chunk c of this lane
-    uint4 q[kUnroll];
+  uint4 q[kUnroll];
+  {
+    const auto r = seg.rsrc();
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) q[u] = stream_load(lp + u * kWave);
-    // the first group sets the reference exponent and the initial threshold
+    for (int u = 0; u < kUnroll; ++u) q[u] = stream_load(r, lane_off, u * (kWave * 16));
+  }
+  // The first group (all of a short segment) sets the reference exponent and the initial threshold: the
+  // K-th largest over the row's wavefronts of each lane's maximum, so that K elements reach it.  Whatever
+  // it lets through is inserted one by one, and each of the row's wavefronts fills a list of its own, so a
+  // short segment spends more on its list than on its stream when the bound is loose: with the least of
+  // K lane groups' maxima, each wavefront's own, 16 rows of 151936 bf16 took 28.4 us, with this one 17.1
+  // (1024 rows: 58.0 and 53.7).
+  {
     float g = -INFINITY;
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {   // unpacked twice: keeps the live registers to one chunk
       float x[VEC];
       unpack(q[u], x);
+      float m = x[0];
 #pragma unroll
-      for (int j = 0; j < VEC; ++j) g = fmaxf(g, x[j]);
+      for (int j = 1; j < VEC; ++j) m = fmaxf(m, x[j]);
+      g = (c0 + u) * kWave + lane < v1 ? fmaxf(g, m) : g;
     }
-    s.mx = wave_max(g);
-    s.r = ceilf(s.mx * kLog2eHi);
-    int kp = 1;
-    while (kp < K) kp <<= 1;
-    const int grp = kWave / kp;           // lanes per group; kp groups
-    float gm = g;
-    for (int o = 1; o < grp; o <<= 1) gm = fmaxf(gm, __shfl_xor(gm, o));
-    for (int o = grp; o < kWave; o <<= 1) gm = fminf(gm, __shfl_xor(gm, o));
-    s.thr = gm;
+    float t = merge_rows(row_sort(g, lane), lane);
+    s.mx = readlane_f(t, 0);
+    if constexpr (S > 1) {
+      if (lane < 16) s_top[wave * 16 + lane] = t;
+      __syncthreads();
+      if constexpr (S <= 4) {
+        t = lane < S * 16 ? s_top[lane] : -INFINITY;
+      } else {
+        t = s_top[lane];
+#pragma unroll
+        for (int w = kWave; w < S * 16; w += kWave) t = row_merge(t, s_top[w + lane], lane);
+      }
+      t = merge_rows(t, lane);
+    }
+    s.thr = readlane_f(t, K - 1);
+    // an element moves the reference only as a candidate, so the reference may not lie below the bound
+    // (a segment that starts with masked logits)
+    s.mx = fmaxf(s.mx, s.thr);
+    s.r = fmaxf(ref_exp(s.mx), kNoExp);
+  }
+  if (c0 < c1) {
     // a ring of kUnroll loads in flight: each chunk's slot (the first group's too) is refilled with the
-    // load kUnroll chunks ahead as soon as its registers are unpacked, before its arithmetic
-    for (; c + 2 * kUnroll <= cfull; c += kUnroll) {
-      lp += kUnroll * kWave;
+    // load kUnroll chunks ahead as soon as its registers are unpacked, before its arithmetic.  The last
+    // group's loads run through the ring as well, zeros past the segment's end: a load that is waited for
+    // alone costs its whole latency, which a short segment would pay up to kUnroll - 1 times
+#pragma unroll 1
+    for (; c + kUnroll < c1; c += kUnroll) {
+      seg.base += kUnroll * kWave * 16;
+      seg.left -= kUnroll * kWave * 16;
+      const auto r = seg.rsrc();
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         float x[VEC];
         unpack(q[u], x);
-        q[u] = stream_load(lp + u * kWave);
-        chunk<VEC>(s, x, true, head + (c + u) * CH, K);
+        q[u] = stream_load(r, lane_off, u * (kWave * 16));
+        chunk<VEC>(s, x, true, head + (c + u) * CH, K, lane);
       }
     }
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      float x[VEC];
-      unpack(q[u], x);
-      chunk<VEC>(s, x, true, head + (c + u) * CH, K);
+      if (c + u < c1) {
+        const bool ok = (c + u) * kWave + lane < v1;
+        float x[VEC];
+        unpack(q[u], x);
+        if ((c + u + 1) * kWave > v1) {    // the row's last chunk, of fewer than kWave vectors
+#pragma unroll
+          for (int j = 0; j < VEC; ++j) x[j] = ok ? x[j] : -INFINITY;
+        }
+        chunk<VEC>(s, x, ok, head + (c + u) * CH, K, lane);
+      }
     }
-    c += kUnroll;
   }
-  for (; c < c1; ++c) {   // the last chunks; the row's last one may hold fewer than 64 vectors
-    const bool ok = c * kWave + lane < nv;
-    uint4 q = neg_inf_vec<T>();
-    if (ok) q = stream_load(pv + (int64_t)c * kWave + lane);
-    float x[VEC];
-    unpack(q, x);
-    chunk<VEC>(s, x, ok, head + c * CH, K);
-  }
-  if (wave == S - 1) {    // elements 0 .. head - 1 and head + nv VEC .. V - 1, fewer than 2 VEC in all
-    const int gap = nv * VEC;
-    const auto id_of = [head, gap](int l, int) { return l < head ? l : gap + l; };
-    const int edge = V - gap;
-    if (edge > 0) {
-      const bool ok = lane < edge;
-      edge_step(s, ok ? to_f32(rowp[id_of(lane, 0)]) : -INFINITY, ok, id_of, K);
-    }
+  if (edge > 0) {
+    asm volatile("" : "+v"(edge_raw));     // the value is first wanted here: no wait for it before the stream
+    const float x = __uint_as_float(sizeof(T) == 2 ? edge_raw << 16 : edge_raw);
+    edge_step(s, lane < edge ? x : -INFINITY, lane < edge, edge_id, K, lane);
   }
 
   // wave sum of the per-lane accumulators (fixed order: a DPP scan, the total in the last lane)
   const double acc = xp::rl_d(xp::wave_incl_scan(s.acc), kWave - 1);
-  if (S > 1) {
-    if (S * K <= kWave) {
-      if (lane < K) {
-        s_key[wave * K + lane] = order_key(s.lv, s.lid);
-        s_kv[wave * K + lane] = s.lv;
-        s_kr[wave * K + lane] = s.lr;
-      }
-    } else if (lane < 16) {
-      s_lv[wave][lane] = s.lv; s_lid[wave][lane] = s.lid; s_lr[wave][lane] = s.lr;
-    }
+  const int n = S * K;                    // candidates: every wave's K best, wave w's at w K .. w K + K - 1
+  if (S > 1 && lane < K) {
+    s_key[wave * K + lane] = order_key(s.lv, s.lid);
+    s_kv[wave * K + lane] = s.lv;
+    s_kr[wave * K + lane] = s.lr;
   }
   if (lane == 0) { s_acc[wave] = acc; s_r[wave] = s.r; }
+  if (wave == 0 && lane < K) s_sel[lane] = lane;   // a valid index in every slot, whatever the row holds
   __syncthreads();
+  if (S > 1) {
+    // One candidate a thread, over as many waves as that takes: its rank among all of them is its slot in
+    // the merged list.  Real entries have distinct keys (ids are distinct); the padding of a segment with
+    // fewer than K elements shares one key below every real one.  The row holds at least K elements, so
+    // slots 0 .. K - 1 each receive exactly one candidate, a real one.
+    // (Inserting the waves' lists one by one, as products S K above 64 did, is a chain of S K dependent
+    // steps on one wave.)
+    const int me = threadIdx.x;
+    if (me < n) {
+      const uint64_t key = s_key[me];
+      int rank = 0;
+#pragma unroll 4
+      for (int j = 0; j < n; ++j) rank += s_key[j] > key ? 1 : 0;
+      if (rank < K) s_sel[rank] = me;
+    }
+    if (n > kWave) __syncthreads();
+  }
   if (wave != 0) return;
-
-  if (S == 1) {
-    // one wave per row: its list is the row's
-  } else if (S * K <= kWave) {
-    // every wave's K best, one per lane: a lane's rank among them is its slot in the merged list.  Real
-    // entries have distinct keys (ids are distinct); the padding of a segment with fewer than K elements
-    // shares one key below every real one.  Only slots below K are needed, and those hold real entries
-    const int n = S * K;
-    const bool has = lane < n;
-    const uint64_t key = has ? s_key[lane] : 0ull;
-    const uint32_t klo = (uint32_t)key, khi = (uint32_t)(key >> 32);
-    int rank = 0;
-#pragma unroll
-    for (int j = 0; j < S * 16 && j < kWave; ++j) {
-      if (j < n) {
-        const uint64_t kj = ((uint64_t)(uint32_t)readlane_i((int)khi, j) << 32) | (uint32_t)readlane_i((int)klo, j);
-        rank += kj > key ? 1 : 0;
-      }
-    }
-    // the row holds at least K elements, so slots 0 .. K - 1 each receive exactly one lane; the first
-    // store only keeps every slot a valid index
-    if (lane < K) s_sel[lane] = lane;
-    if (has && rank < K) s_sel[rank] = lane;
-    if (lane < K) {
-      const int src = s_sel[lane];
-      s.lid = key_id(s_key[src]);
-      s.lv = s_kv[src];
-      s.lr = s_kr[src];
-    }
-  } else {
-    for (int w = 1; w < S; ++w) {
-      for (int k = 0; k < K; ++k) {
-        const float v = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_lv[w][k])));
-        const int id = __builtin_amdgcn_readfirstlane(s_lid[w][k]);
-        const float rr = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_lr[w][k])));
-        if (!before(v, id, s.thr, s.thr_id)) break;   // the rest of this sorted list cannot enter
-        list_insert(s, v, id, rr, K);
-      }
-    }
+  if (S > 1 && lane < K) {
+    const int src = s_sel[lane];
+    s.lid = key_id(s_key[src]);
+    s.lv = s_kv[src];
+    s.lr = s_kr[src];
   }
   float R = s_r[0];
 #pragma unroll

@@ -1044,3 +1044,39 @@ def test_k1_rows_at_any_alignment(dtype, waves, monkeypatch):
                 assert np.array_equal(h["topk_ids"][b], ref[b]["ids"]), (V, off, b)
                 assert np.array_equal(h["topk_logit"][b].astype(np.float64), ref[b]["logit"]), (V, off, b)
                 assert np.abs(h["lse"][b] - ref[b]["lse"]).max() <= 1e-7, (V, off, b)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("waves", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("K", [1, 5, 16])
+def test_k1_first_group_threshold(dtype, waves, K, monkeypatch):
+    """The initial threshold over the row's wavefronts: rows that end inside a first group, hold ties at the
+    K-th value, or are masked (-inf) from the front, so that some segments start with nothing.  The
+    normaliser is compared in 64 bits at the 1e-7 that every parity test allows."""
+    import torch
+    monkeypatch.setenv("CADDTREE_K1_WAVES", str(waves))
+    vec = 8 if dtype == "bf16" else 4
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rng = np.random.default_rng(11 + waves)
+    for V in (K, 64 * vec, 7 * 64 * vec + 5 * vec, 8 * 64 * vec + vec + 1, 33 * 64 * vec, 130 * 64 * vec + 3):
+        L, B = 3, 2
+        x = (3.0 * rng.standard_normal((B, L, V))).astype(np.float32)
+        x[:, 1] = np.round(x[:, 1] / 2.0)                    # few values: ties at every rank
+        keep = max(K, V // 3)
+        x[:, 2, : V - keep] = -np.inf
+        cfg = synth.get_config("c1").replace(V=V, B=B, L=L, K=K, cap=8, dtype=dtype)
+        plan = make_plan(cfg)
+        logits = torch.from_numpy(x).to(tdt).cuda()
+        out = plan.new_outputs(B, topk=True)
+        plan.reduce_topk(logits, out.topk_ids, out.topk_logit, out.lse, out.topk_lq)
+        torch.cuda.synchronize()
+        h = host(out)
+        xd = logits.cpu().to(torch.float64).numpy()
+        for b in range(B):
+            for i in range(L):
+                order = np.argsort(-xd[b, i], kind="stable")[:K]
+                assert np.array_equal(h["topk_ids"][b, i], order), (V, b, i)
+                assert np.array_equal(h["topk_logit"][b, i].astype(np.float64), xd[b, i][order]), (V, b, i)
+                m = xd[b, i].max()
+                lse = m + np.log(np.exp(xd[b, i] - m).sum())
+                assert abs(h["lse"][b, i] - lse) <= 1e-7, (V, b, i)
