@@ -113,7 +113,12 @@ class TreeOutputs:
 
 
 class Plan:
-    """An immutable CaDDTree plan (shape limits, dtype, mask format, cost model)."""
+    """An immutable CaDDTree plan (shape limits, dtype, mask format, cost model).
+
+    Each call goes to the native binding first, which checks the tensors and calls the library; what it
+    cannot vouch for comes back as None and takes the Python checks here, which raise what is wrong."""
+
+    _fast = None            # the native calls' view of the plan
 
     def __init__(self, L: int, V: int, K: int, cap: int, t_draft: float, t_verify,
                  dtype: str = "bf16", mask: str = "u8", allow_nonconvex: bool = False,
@@ -148,9 +153,12 @@ class Plan:
         _lib.check(self._lib.caddtree_plan_create(ctypes.byref(cfg), ctypes.byref(h)))
         self._h = h
         self.device = _torch().cuda.current_device()   # the library binds the plan to this device
+        self._native = _lib.binding()
+        self._fast = _lib.call_spec(self._lib, h.value, self.device, self.L, self.V, self.K, self.cap, dtype, mask)
 
     # ------------------------------------------------------------ lifetime
     def close(self) -> None:
+        self._fast = None
         h = getattr(self, "_h", None)
         if h is not None and h.value:
             self._lib.caddtree_plan_destroy(h)
@@ -200,7 +208,13 @@ class Plan:
             out.lse = torch.empty((B, self.L), dtype=torch.float64, device=dev)
         return out
 
-    # ------------------------------------------------------------ calls
+    def _raw_stream(self, stream):
+        """The stream's handle for a native call; None for a form that the Python path decides."""
+        torch = _torch()
+        if stream is None:
+            return torch._C._cuda_getCurrentRawStream(self.device)
+        return stream.cuda_stream if isinstance(stream, torch.cuda.Stream) else None
+
     # ------------------------------------------------------------ argument checks (before any C call)
     def _logits(self, logits):
         torch = _torch()
@@ -274,6 +288,13 @@ class Plan:
 
     def build(self, logits, out: TreeOutputs, pos_offset: int = 0, workspace=None, stream=None,
               ctx_len=None) -> None:
+        if self._fast is not None:
+            status = self._native.build(self._fast, logits, out, pos_offset, workspace, ctx_len,
+                                        self._raw_stream(stream), False)
+            if status is not None:
+                if status:
+                    _lib.check(status)
+                return
         B, stride = self._logits(logits)
         self._tree(B, out)
         self._tree(B, out, emit=True)
@@ -289,6 +310,13 @@ class Plan:
         """``build`` without a workspace (``caddtree_build_noalloc``): the top-K table not asked for in
         ``out`` lives in the library's own device array, shared by every such call on the GPU, so calls
         that overlap in time on one GPU race."""
+        if self._fast is not None:
+            status = self._native.build(self._fast, logits, out, pos_offset, None, ctx_len,
+                                        self._raw_stream(stream), True)
+            if status is not None:
+                if status:
+                    _lib.check(status)
+                return
         B, stride = self._logits(logits)
         self._tree(B, out)
         self._tree(B, out, emit=True)
@@ -299,6 +327,13 @@ class Plan:
                                                     ctypes.byref(st), _stream(stream, logits.device)))
 
     def reduce_topk(self, logits, topk_ids, topk_logit, lse, topk_lq=None, stream=None) -> None:
+        if self._fast is not None:
+            status = self._native.reduce_topk(self._fast, logits, topk_ids, topk_logit, lse, topk_lq,
+                                              self._raw_stream(stream))
+            if status is not None:
+                if status:
+                    _lib.check(status)
+                return
         B, stride = self._logits(logits)
         self._topk(B, topk_ids, topk_logit, lse, topk_lq)
         _lib.check(self._lib.caddtree_reduce_topk(self._h, _ptr(logits), B, stride, _ptr(topk_ids),
@@ -306,6 +341,13 @@ class Plan:
                                                   _stream(stream, logits.device)))
 
     def expand(self, topk_ids, topk_logit, lse, out: TreeOutputs, stream=None, ctx_len=None) -> None:
+        if self._fast is not None:
+            status = self._native.expand(self._fast, topk_ids, topk_logit, lse, out, ctx_len,
+                                         self._raw_stream(stream))
+            if status is not None:
+                if status:
+                    _lib.check(status)
+                return
         self._topk(0, topk_ids, topk_logit, lse)
         B = int(topk_ids.shape[0])
         self._topk(B, topk_ids, topk_logit, lse)
@@ -321,6 +363,13 @@ class Plan:
         """Synthetic acceptance of ``tree`` (built from the top-K table in ``topk``) against target paths
         drawn from the uniforms ``u`` (float64 [B, L]); writes ``accept_len`` (int32 [B]) and optionally
         ``round_cost`` (float64 [B], this plan's C_d + C_v(n*))."""
+        if self._fast is not None:
+            status = self._native.accept(self._fast, topk, tree, u, accept_len, round_cost, ctx_len,
+                                         self._raw_stream(stream))
+            if status is not None:
+                if status:
+                    _lib.check(status)
+                return
         torch = _torch()
         if not isinstance(tree.token_ids, torch.Tensor) or tree.token_ids.dim() != 2:
             raise ValueError("tree.token_ids must be a [B, tree_stride] tensor")
@@ -342,6 +391,12 @@ class Plan:
                                              _stream(stream, u.device)))
 
     def emit(self, out: TreeOutputs, pos_offset: int = 0, stream=None) -> None:
+        if self._fast is not None:
+            status = self._native.emit(self._fast, out, pos_offset, self._raw_stream(stream))
+            if status is not None:
+                if status:
+                    _lib.check(status)
+                return
         _check("parent", out.parent, _torch().int32, (max(self.cap, 1),), 0, self.device)
         B = int(out.parent.shape[0])
         self._tree(B, out, emit=True)

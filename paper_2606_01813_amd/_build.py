@@ -7,10 +7,12 @@ Every HIP translation unit is compiled with packed fp32 instructions disabled
 from __future__ import annotations
 
 import concurrent.futures as cf
+import importlib.util
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -22,6 +24,9 @@ PROBE_LIB = os.path.join(PKG, "libcaddtree_probe.so")
 PROBE_SOURCES = ["probe.hip"]
 SOURCES = ["api.cpp", "reduce_topk.hip", "expand.hip", "expand_level.hip", "expand_wide.hip", "emit.hip", "accept.hip",
            "scratch.hip", "costfit.cpp"]
+# the Python binding's native calls (host code, against torch's headers): an extension module
+BINDING = os.path.join(PKG, "_binding.so")
+BINDING_SOURCE = "binding.cpp"
 ARCH = os.environ.get("CADDTREE_ARCH", "gfx950")
 
 
@@ -38,10 +43,21 @@ def common_flags():
             "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument"]
 
 
+def torch_dir() -> str:
+    return os.path.dirname(importlib.util.find_spec("torch").origin)
+
+
+def binding_flags():
+    inc = os.path.join(torch_dir(), "include")
+    return ["-D__HIP_PLATFORM_AMD__=1", "-I", sysconfig.get_paths()["include"], "-isystem", inc,
+            "-isystem", os.path.join(inc, "torch", "csrc", "api", "include")]
+
+
 def _compile(src: str, obj_dir: str, verbose: bool) -> str:
     obj = os.path.join(obj_dir, os.path.splitext(src)[0] + ".o")
     lang = ["-x", "hip"] if src.endswith(".hip") else []
-    cmd = [hipcc()] + common_flags() + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
+    extra = binding_flags() if src == BINDING_SOURCE else []
+    cmd = [hipcc()] + common_flags() + extra + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -52,9 +68,9 @@ def _compile(src: str, obj_dir: str, verbose: bool) -> str:
     return obj
 
 
-def _link(objs, out: str, verbose: bool) -> None:
+def _link(objs, out: str, verbose: bool, libs=()) -> None:
     tmp = out + ".tmp"
-    cmd = [hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp] + objs
+    cmd = [hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp] + objs + list(libs)
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -66,11 +82,13 @@ def _link(objs, out: str, verbose: bool) -> None:
 def build(verbose: bool = False) -> str:
     obj_dir = os.path.join(PKG, "_build")
     os.makedirs(obj_dir, exist_ok=True)
-    srcs = SOURCES + PROBE_SOURCES
+    srcs = SOURCES + PROBE_SOURCES + [BINDING_SOURCE]
     with cf.ThreadPoolExecutor(max_workers=len(srcs)) as ex:
         objs = dict(zip(srcs, ex.map(lambda s: _compile(s, obj_dir, verbose), srcs)))
     _link([objs[s] for s in SOURCES], LIB, verbose)
     _link([objs[s] for s in PROBE_SOURCES], PROBE_LIB, verbose)
+    _link([objs[BINDING_SOURCE]], BINDING, verbose,
+          ["-L" + os.path.join(torch_dir(), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"])
     return LIB
 
 

@@ -107,3 +107,27 @@ def check(status: int) -> None:
         msg = lib().caddtree_last_error().decode(errors="replace")
         name = lib().caddtree_status_string(status).decode()
         raise CaddtreeError(status, f"{name}: {msg}")
+
+
+_BINDING = None
+
+
+def binding():
+    """The native calls of the binding (csrc/binding.cpp)."""
+    global _BINDING
+    if _BINDING is None:
+        path = os.path.join(_HERE, "_binding.so")
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is missing: build the library first (python -m paper_2606_01813_amd._build)")
+        import torch  # noqa: F401  (the module uses torch's libraries)
+        from . import _binding
+        _BINDING = _binding
+    return _BINDING
+
+
+def call_spec(lib_, handle: int, device: int, L: int, V: int, K: int, cap: int, dtype: str, mask: str):
+    """What the native calls need of a plan: its handle, the shapes of its tensors and the library's functions."""
+    fns = (lib_.caddtree_build, lib_.caddtree_build_noalloc, lib_.caddtree_reduce_topk, lib_.caddtree_expand,
+           lib_.caddtree_emit, lib_.caddtree_accept)
+    return binding().spec(handle, device, L, V, K, cap, DTYPES[dtype], MASKS[mask],
+                          *(ctypes.cast(f, ctypes.c_void_p).value for f in fns))
