@@ -122,8 +122,11 @@ caddtree_status_t caddtree_plan_create(const caddtree_config_t* cfg, caddtree_pl
 /* Frees the plan (NULL is a no-op).  The caller ensures no enqueued work still uses it. */
 void caddtree_plan_destroy(caddtree_plan_t plan);
 
-/* Device workspace caddtree_build needs for B rounds (the top-K table when the
- * caller does not ask for it).  256-byte alignment is required. */
+/* Device workspace caddtree_build uses for B rounds: the top-K table when the
+ * caller does not ask for it, and for a few rounds the partial results of rows
+ * that several workgroups reduce (a workspace that holds the table alone is
+ * accepted; such a call reduces a row in one workgroup).  256-byte alignment is
+ * required. */
 size_t caddtree_workspace_bytes(caddtree_plan_t plan, int64_t B);
 
 /* Outputs of caddtree_build (DEVICE pointers).  Required: token_ids, parent,
@@ -169,7 +172,7 @@ typedef struct {
  * tree T*_{n*} of eq. phistar at n* = the first maximiser of eq. per-round,
  * Cor. 2), and the tree-attention mask and position ids (Sec. 3.3).
  * logits: DEVICE [B, L, row_stride] of the plan's dtype; B >= 0 (0 is a no-op).
- * workspace: DEVICE, >= caddtree_workspace_bytes(plan, B) bytes, 256-byte aligned
+ * workspace: DEVICE, caddtree_workspace_bytes(plan, B) bytes, 256-byte aligned
  * (may be NULL when every top-K output pointer is given).
  * The call only enqueues kernels on `stream` (no allocation, memset or
  * synchronisation), so it may be captured in a HIP graph; a replay reads and

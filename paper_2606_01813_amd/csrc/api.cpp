@@ -31,6 +31,7 @@ struct caddtree_plan {
   int level_set_cap;    // its threshold-set capacity
   int device;
   int k1_waves;         // 0 = automatic
+  int k1_split;         // 0 = automatic
   int k1_unroll;        // 0 = automatic
   bool noalloc_ready;   // the scratch array of caddtree_build_noalloc has an address on this device
   bool fuse_emit;       // caddtree_build lets the expansion's epilogue write the mask and position ids
@@ -106,6 +107,21 @@ size_t topk_workspace(const caddtree_plan* p, int64_t B, const caddtree_outputs_
   return off;
 }
 
+// The launch shape of a reduction of `rows` rows; may_split: there is memory for partial results.
+caddtree::ReduceShape reduce_shape(const caddtree_plan* p, int64_t rows, bool may_split) {
+  return caddtree::reduce_default_shape(rows, (int32_t)p->V, p->K, p->dtype, may_split);
+}
+
+// The parts of a row in a build of B rounds with `bytes` of workspace past the top-K table's (1: not split),
+// and the bytes they take.
+int32_t build_split(const caddtree_plan* p, int64_t B, size_t bytes, size_t* need) {
+  const int64_t rows = B * p->L;
+  const int32_t split = p->k1_split > 0 ? p->k1_split : reduce_shape(p, rows, true).split;
+  *need = split > 1 ? (size_t)rows * (size_t)caddtree::split_row_bytes(p->K, split) : 0;
+  if (*need > bytes) return 1;
+  return split;
+}
+
 caddtree_status_t check_logits(const caddtree_plan* p, const void* logits, int64_t B, int64_t row_stride) {
   if (B < 0) return fail(CADDTREE_E_INVALID, "B = %lld is negative", (long long)B);
   if (B > 0 && logits == nullptr) return fail(CADDTREE_E_INVALID, "logits is NULL");
@@ -118,14 +134,17 @@ caddtree_status_t check_logits(const caddtree_plan* p, const void* logits, int64
 
 
 caddtree_status_t run_reduce(const caddtree_plan* p, const void* logits, int64_t B, int64_t row_stride,
-                             int32_t* ids, float* logit, float* lq, double* lse, hipStream_t stream) {
+                             int32_t* ids, float* logit, float* lq, double* lse, hipStream_t stream,
+                             int32_t split = 1, void* parts = nullptr) {
   caddtree::ReduceArgs a;
   a.logits = logits;
   a.rows = B * p->L;
   a.row_stride = row_stride;
   a.V = (int32_t)p->V;
   a.K = p->K;
-  const caddtree::ReduceShape sh = caddtree::reduce_default_shape(a.rows, (int32_t)p->V, p->dtype);
+  const caddtree::ReduceShape sh = reduce_shape(p, a.rows, false);
+  a.split = split;
+  a.parts = parts;
   a.waves_per_row = p->k1_waves > 0 ? p->k1_waves : sh.waves;
   a.unroll = p->k1_unroll > 0 ? p->k1_unroll : sh.unroll;
   a.ids = ids;
@@ -146,8 +165,10 @@ caddtree_status_t check_ctx(const caddtree_plan* p, const int64_t* ctx_len) {
 caddtree_status_t run_expand(const caddtree_plan* p, const int32_t* ids, const float* logit, const double* lse,
                              int64_t B, const int64_t* ctx_len, int32_t* token_ids, int32_t* parent,
                              int32_t* depth, float* path_prob, int32_t* n_star, float* phi, float* theta,
-                             hipStream_t stream, const caddtree::EmitOut* em = nullptr) {
+                             hipStream_t stream, const caddtree::EmitOut* em = nullptr,
+                             const caddtree::MergeIn* merge = nullptr) {
   caddtree::ExpandArgs a;
+  a.merge = merge ? *merge : caddtree::MergeIn{};
   a.em = em ? *em : caddtree::EmitOut{nullptr, nullptr, (int)CADDTREE_MASK_NONE, 0};
   a.topk_ids = ids;
   a.topk_logit = logit;
@@ -353,6 +374,11 @@ caddtree_status_t caddtree_plan_create(const caddtree_config_t* cfg, caddtree_pl
     const int w = std::atoi(env);
     if (w == 1 || w == 2 || w == 4 || w == 8 || w == 16) p->k1_waves = w;
   }
+  p->k1_split = 0;
+  if (const char* env = std::getenv("CADDTREE_K1_SPLIT")) {
+    const int x = std::atoi(env);
+    if (x >= 1 && x * p->K <= 64 && (x & (x - 1)) == 0) p->k1_split = x;
+  }
   p->k1_unroll = 0;
   if (const char* env = std::getenv("CADDTREE_K1_UNROLL")) {
     const int u = std::atoi(env);
@@ -397,7 +423,9 @@ void caddtree_plan_destroy(caddtree_plan_t p) {
 size_t caddtree_workspace_bytes(caddtree_plan_t p, int64_t B) {
   if (p == nullptr || B <= 0) return 0;
   TopkBuffers tb;
-  return topk_workspace(p, B, nullptr, nullptr, &tb);
+  size_t split = 0;
+  build_split(p, B, SIZE_MAX, &split);
+  return topk_workspace(p, B, nullptr, nullptr, &tb) + align256(split);
 }
 
 caddtree_status_t caddtree_reduce_topk(caddtree_plan_t p, const void* logits, int64_t B, int64_t row_stride,
@@ -474,17 +502,30 @@ caddtree_status_t check_build(const caddtree_plan* p, const void* logits, int64_
 // The three stages on `stream`, the top-K table the caller did not ask for carved from `workspace`.
 caddtree_status_t run_build(const caddtree_plan* p, const void* logits, int64_t B, int64_t row_stride,
                             int32_t pos_offset, const int64_t* ctx_len, const caddtree_outputs_t* out,
-                            void* workspace, hipStream_t stream) {
+                            void* workspace, size_t workspace_bytes, hipStream_t stream) {
   TopkBuffers tb;
-  topk_workspace(p, B, out, static_cast<char*>(workspace), &tb);
+  const size_t table = topk_workspace(p, B, out, static_cast<char*>(workspace), &tb);
+  // what is left of the workspace holds a split reduction's parts; without a workspace, or with one of the
+  // table's size alone, a row is one workgroup's
+  size_t need = 0;
+  const bool room = workspace != nullptr && workspace_bytes >= table && reinterpret_cast<uintptr_t>(workspace) % 256 == 0;
+  const int32_t split = room ? build_split(p, B, workspace_bytes - table, &need) : 1;
+  void* parts = split > 1 ? static_cast<char*>(workspace) + table : nullptr;
+  const caddtree::MergeIn merge{parts, split, tb.ids, tb.logit, out->topk_lq, tb.lse};
   caddtree_status_t st;
-  if ((st = run_reduce(p, logits, B, row_stride, tb.ids, tb.logit, out->topk_lq, tb.lse, stream)) != CADDTREE_OK)
+  if ((st = run_reduce(p, logits, B, row_stride, tb.ids, tb.logit, out->topk_lq, tb.lse, stream, split, parts)) !=
+      CADDTREE_OK)
     return st;
+  const bool prologue = split > 1 && caddtree::expand_merges(p->use_level, p->use_wide);
+  if (split > 1 && !prologue) {
+    const hipError_t e = caddtree::launch_merge(merge, B * p->L, p->K, stream);
+    if (e != hipSuccess) return hip_fail(e, "merge launch");
+  }
   caddtree::EmitOut em{p->mask == CADDTREE_MASK_NONE ? nullptr : out->mask, out->pos_ids, (int)p->mask, pos_offset};
   const bool fused = p->fuse_emit && p->cap > 0;
   if ((st = run_expand(p, tb.ids, tb.logit, tb.lse, B, ctx_len, out->token_ids, out->parent, out->depth,
-                       out->path_prob, out->n_star, out->phi, out->theta, stream, fused ? &em : nullptr)) !=
-      CADDTREE_OK)
+                       out->path_prob, out->n_star, out->phi, out->theta, stream, fused ? &em : nullptr,
+                       prologue ? &merge : nullptr)) != CADDTREE_OK)
     return st;
   if (!fused &&
       (st = run_emit(p, out->parent, out->depth, out->n_star, B, pos_offset, out->mask, out->pos_ids, stream)) !=
@@ -513,7 +554,7 @@ caddtree_status_t caddtree_build(caddtree_plan_t p, const void* logits, int64_t 
     if (workspace_bytes < need)
       return fail(CADDTREE_E_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
   }
-  return run_build(p, logits, B, row_stride, pos_offset, ctx_len, out, workspace, stream);
+  return run_build(p, logits, B, row_stride, pos_offset, ctx_len, out, workspace, workspace_bytes, stream);
 }
 
 caddtree_status_t caddtree_build_noalloc(caddtree_plan_t p, const void* logits, int64_t B, int64_t row_stride,
@@ -525,17 +566,15 @@ caddtree_status_t caddtree_build_noalloc(caddtree_plan_t p, const void* logits, 
   if (done) return ok();
   TopkBuffers tb;
   const size_t need = topk_workspace(p, B, out, nullptr, &tb);
+  if (need > caddtree::kNoAllocScratchBytes)
+    return fail(CADDTREE_E_WORKSPACE,
+                "the top-K table of %lld rounds needs %zu bytes, beyond the %zu-byte library scratch; pass the "
+                "top-K outputs or use caddtree_build with a workspace",
+                (long long)B, need, caddtree::kNoAllocScratchBytes);
   void* scratch = nullptr;
-  if (need > 0) {
-    if (need > caddtree::kNoAllocScratchBytes)
-      return fail(CADDTREE_E_WORKSPACE,
-                  "the top-K table of %lld rounds needs %zu bytes, beyond the %zu-byte library scratch; pass the "
-                  "top-K outputs or use caddtree_build with a workspace",
-                  (long long)B, need, caddtree::kNoAllocScratchBytes);
-    if (!p->noalloc_ready || (scratch = caddtree::noalloc_scratch(p->device)) == nullptr)
-      return fail(CADDTREE_E_HIP, "the library scratch has no address on device %d", p->device);
-  }
-  return run_build(p, logits, B, row_stride, pos_offset, ctx_len, out, scratch, stream);
+  if (need > 0 && (!p->noalloc_ready || (scratch = caddtree::noalloc_scratch(p->device)) == nullptr))
+    return fail(CADDTREE_E_HIP, "the library scratch has no address on device %d", p->device);
+  return run_build(p, logits, B, row_stride, pos_offset, ctx_len, out, scratch, caddtree::kNoAllocScratchBytes, stream);
 }
 
 caddtree_status_t caddtree_accept(caddtree_plan_t p, const int32_t* topk_ids, const float* topk_logit,

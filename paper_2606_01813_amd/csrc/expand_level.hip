@@ -67,6 +67,7 @@
 
 #include "expand_level.h"
 #include "expand_serial.h"
+#include "reduce_merge.h"
 
 namespace caddtree {
 namespace {
@@ -76,20 +77,84 @@ namespace {
 // crowd the batched kernel's registers.
 __device__ __attribute__((noinline)) void serial_in_place(serial::Args a, int b) { serial::expand_round(a, b); }
 
-__global__ void __launch_bounds__(kW)
+// The prologue of a round whose rows several workgroups reduced: a wavefront per row (rows w, w + 8, ..)
+// merges its parts into the top-K table, in LDS and in memory.
+constexpr int kMergeWaves = 8;
+__device__ __forceinline__ void merge_round(const MergeIn& mg, int b, int L, int K, const Lds& s, double* lse_sh,
+                                            int w, int lane) {
+  constexpr int kRows = CADDTREE_MAX_L / kMergeWaves;      // rows a wavefront, at most
+  red::PartRegs m[kRows];
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {                        // every row's loads before the first merge
+    const int i = w + u * kMergeWaves;
+    if (i < L) m[u].load(red::part_row(mg.parts, (int64_t)b * L + i, K, mg.split), K, mg.split, lane);
+  }
+  float v[kRows];
+  double sum = 1.0;                                        // lane u: row u's
+  float R = 0.f;
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    const int i = w + u * kMergeWaves;
+    if (i < L) {
+      int id;
+      red::merge_list(m[u], K * mg.split, lane, v[u], id);
+      double su;
+      float Ru;
+      red::merge_sum(m[u], mg.split, su, Ru);
+      if (lane == u) { sum = su; R = Ru; }
+      if (lane < K) {
+        const int64_t o = ((int64_t)b * L + i) * K + lane;
+        s.tl[i * K + lane] = v[u];
+        s.tid[i * K + lane] = id;
+        mg.ids[o] = id;
+        mg.logit[o] = v[u];
+      }
+    }
+  }
+  const double lse = red::lse_of(sum, R);                  // every row's at once
+  if (lane < kRows && w + lane * kMergeWaves < L) {
+    lse_sh[w + lane * kMergeWaves] = lse;
+    mg.lse[(int64_t)b * L + w + lane * kMergeWaves] = lse;
+  }
+  if (mg.lq) {
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      const int i = w + u * kMergeWaves;
+      const double l = rl_d(lse, u);
+      if (i < L && lane < K) mg.lq[((int64_t)b * L + i) * K + lane] = (float)((double)v[u] - l);
+    }
+  }
+}
+
+// kMerge: the round's table comes from a split reduction's parts; kMergeWaves wavefronts merge it and all
+// but the first end there (a barrier does not wait for wavefronts that have ended)
+template <bool kMerge>
+__global__ void __launch_bounds__(kMerge ? kMergeWaves * kW : kW)
 expand_level_kernel(const int32_t* __restrict__ topk_ids, const float* __restrict__ topk_logit,
                     const double* __restrict__ lse, int L, int K, int cap, CostTables ct, int fixed,
                     int flat, int setcap, int32_t* __restrict__ token_ids,
                     int32_t* __restrict__ parent_out, int32_t* __restrict__ depth_out,
                     float* __restrict__ path_prob, int32_t* __restrict__ n_star_out,
                     float* __restrict__ phi_out, float* __restrict__ theta_out, int in_place, EmitOut em,
-                    int first_rise, double tau_model) {
+                    int first_rise, double tau_model, MergeIn mg) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = blockIdx.x;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & (kW - 1);
   const int LK = L * K;
   const bool lean = fixed || flat;          // no cost table
   const Lds s = carve(smem, (size_t)LK, (size_t)setcap, lean);
+  double lse_m = 0.0;
+  if constexpr (kMerge) {
+    __shared__ double lse_sh[CADDTREE_MAX_L];
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kW);
+    merge_round(mg, b, L, K, s, lse_sh, w, lane);
+    __syncthreads();
+    if (w != 0) return;
+    lse_m = lse_sh[lane < L ? lane : L - 1];
+    topk_ids = mg.ids;                       // for the serial form
+    topk_logit = mg.logit;
+    lse = mg.lse;
+  }
   const RoundCost rc = round_cost_wave(ct, b, lane);
   // the level build's lane split: group grp of K lanes takes one parent, lane rk of it one rank
   constexpr int kPasses = 4;               // passes a step
@@ -104,9 +169,11 @@ expand_level_kernel(const int32_t* __restrict__ topk_ids, const float* __restric
   // clamped rather than guarded (a clamped lane loads and stores the same value as the last
   // valid one), so neither loads nor stores sit behind branches.
   const double c0 = rc(0);
-  const double lse_l = lse[(int64_t)b * L + (lane < L ? lane : L - 1)];
+  const double lse_l = kMerge ? lse_m : lse[(int64_t)b * L + (lane < L ? lane : L - 1)];
   CostCache cc{rc, s.cw, cap, lean ? 0 : (cap < setcap ? cap : setcap) + 2, 0};   // C(0 .. ncw - 1)
-  {
+  if constexpr (kMerge) {
+    cc.ensure(kW + 2, lane);
+  } else {
     constexpr int kT = CADDTREE_MAX_L * CADDTREE_MAX_K / kW;        // top-K entries per lane, at most
     float lv[kT];
     int32_t iv[kT];
@@ -434,7 +501,10 @@ int expand_level_max_need(bool lean) { return lean ? kMaxLeanSet * 4 / 5 : kMaxS
 size_t expand_level_lds_limit() { return kMaxLds; }
 
 hipError_t expand_level_prepare() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&expand_level_kernel),
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&expand_level_kernel<false>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&expand_level_kernel<true>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
 }
 
@@ -443,10 +513,13 @@ hipError_t launch_expand_level(const ExpandArgs& a, size_t in_place_lds, hipStre
   const bool lean = a.fixed_budget || a.flat_cost;
   size_t lds = expand_level_lds_bytes(a.L, a.K, a.level_set_cap, lean);
   if (in_place_lds > lds) lds = in_place_lds;
-  hipLaunchKernelGGL(expand_level_kernel, dim3((unsigned)a.B), dim3(kW), lds, stream, a.topk_ids, a.topk_logit,
-                     a.lse, a.L, a.K, a.cap, a.cost, a.fixed_budget ? 1 : 0, (!a.fixed_budget && a.flat_cost) ? 1 : 0,
-                     a.level_set_cap, a.token_ids, a.parent, a.depth, a.path_prob, a.n_star, a.phi, a.theta,
-                     in_place_lds > 0 ? 1 : 0, a.em, a.first_rise, a.tau_model);
+  const bool merge = a.merge.parts != nullptr;
+  const auto kernel = merge ? expand_level_kernel<true> : expand_level_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)a.B), dim3(merge ? kMergeWaves * kW : kW), lds, stream, a.topk_ids,
+                     a.topk_logit, a.lse, a.L, a.K, a.cap, a.cost, a.fixed_budget ? 1 : 0,
+                     (!a.fixed_budget && a.flat_cost) ? 1 : 0, a.level_set_cap, a.token_ids, a.parent, a.depth,
+                     a.path_prob, a.n_star, a.phi, a.theta, in_place_lds > 0 ? 1 : 0, a.em, a.first_rise, a.tau_model,
+                     a.merge);
   return hipGetLastError();
 }
 

@@ -21,6 +21,8 @@ struct ReduceArgs {
   int32_t K;
   int32_t waves_per_row; // 1 .. 16
   int32_t unroll;        // 16-byte loads in flight per lane: 4 or 8
+  int32_t split;         // parts a row is cut into, a workgroup each; above 1 the results go to `parts`
+  void* parts;           // [rows, split_row_bytes(K, split)] when split > 1
   int32_t* ids;          // [rows, K]
   float* logit;          // [rows, K]
   float* lq;             // [rows, K] or nullptr
@@ -30,8 +32,22 @@ hipError_t launch_reduce_topk(const ReduceArgs& a, caddtree_dtype_t dtype, hipSt
 struct ReduceShape {
   int32_t waves;   // waves per row
   int32_t unroll;  // 16-byte loads in flight per lane
+  int32_t split;   // parts per row
 };
-ReduceShape reduce_default_shape(int64_t rows, int32_t V, caddtree_dtype_t dtype);
+ReduceShape reduce_default_shape(int64_t rows, int32_t V, int32_t K, caddtree_dtype_t dtype, bool may_split);
+// a row's partial results: per part a sum (fp64) and its exponent, and K keys (64 bits) and values
+constexpr int32_t split_row_bytes(int32_t K, int32_t split) { return (split * (12 + 12 * K) + 15) / 16 * 16; }
+
+// A split reduction's partial results, and where the merged table goes.
+struct MergeIn {
+  void* parts;           // null: the table is there already
+  int32_t split;
+  int32_t* ids;          // [B, L, K]
+  float* logit;          // [B, L, K]
+  float* lq;             // [B, L, K] or nullptr
+  double* lse;           // [B, L]
+};
+hipError_t launch_merge(const MergeIn& mg, int64_t rows, int32_t K, hipStream_t stream);
 
 // Stage 2: best-first expansion with the greedy stop, one workgroup per round.
 struct ExpandArgs {
@@ -58,7 +74,10 @@ struct ExpandArgs {
                            // -1 if none; -2 when the kernel finds it per round (several tables)
   double tau_model;        // with first_rise = m0 >= 0: log(2 (C(m0 + 1) - C(m0)) / C(min(m0 + 32, cap))) - 1/2
   EmitOut em;              // mask and position ids written by the expansion's epilogue (null: not here)
+  MergeIn merge;           // parts the expansion merges first; only where expand_merges() says so
 };
+// the expansion kernel of a plan merges a split reduction's parts in its prologue
+inline bool expand_merges(bool use_level, bool use_wide) { return use_level && !use_wide; }
 size_t expand_lds_bytes(int32_t L, int32_t K, int32_t cap);
 hipError_t expand_prepare(int32_t L, int32_t K, int32_t cap);  // raises the dynamic-LDS limit once
 hipError_t launch_expand(const ExpandArgs& a, hipStream_t stream);

@@ -33,17 +33,14 @@
 
 #include "expand_common.h"
 #include "internal.h"
+#include "reduce_merge.h"
 
 namespace caddtree {
 namespace {
 
-constexpr int kWave = 64;
-constexpr float kLog2eHi = 0x1.715476p+0f;     // log2(e) rounded to fp32
-constexpr float kLog2eLo = 0x1.4ae0c0p-26f;    // log2(e) - kLog2eHi, rounded to fp32
-constexpr double kLog2eD = 0x1.71547652b82fep+0;
-constexpr double kLn2D = 0x1.62e42fefa39efp-1;
-constexpr float kNoExp = -1.0e30f;             // "no reference exponent yet"
+using namespace red;
 
+constexpr int kWave = 64;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Streaming 16-byte loads of a wavefront's segment, with the non-temporal hint (each byte of the logits is
@@ -145,12 +142,6 @@ __device__ __forceinline__ float merge_rows(float v, int lane) {
 // (v, id) goes before (w, wid) in the order value desc, id asc
 __device__ __forceinline__ bool before(float v, int id, float w, int wid) {
   return v > w || (v == w && id < wid);
-}
-
-__device__ __forceinline__ float term(float x, float r) {
-  float a = fmaf(x, kLog2eHi, -r);
-  a = fmaf(x, kLog2eLo, a);
-  return __builtin_amdgcn_exp2f(a);
 }
 
 // The reference exponent for a running maximum of mx: terms of up to 2^3.  The hardware exp2's error is
@@ -287,23 +278,12 @@ __device__ __forceinline__ void unpack(const uint4& q, float (&x)[4]) {
 __device__ __forceinline__ uint32_t raw_bits(const float* p) { return __float_as_uint(*p); }
 __device__ __forceinline__ uint32_t raw_bits(const uint16_t* p) { return *p; }
 
-// (value, id) as one unsigned 64-bit key whose order is the top-K order: the value's bits mapped
-// to an unsigned integer that grows with the value (-0 taken as +0, which compares equal to it),
-// then INT_MAX - id (smaller ids first)
-__device__ __forceinline__ uint64_t order_key(float v, int id) {
-  uint32_t b = (uint32_t)__float_as_int(v);
-  if (b == 0x80000000u) b = 0u;
-  const uint32_t u = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-  return ((uint64_t)u << 32) | (uint32_t)(INT_MAX - id);
-}
-__device__ __forceinline__ int key_id(uint64_t k) { return INT_MAX - (int)(uint32_t)k; }
-
 // kUnroll: 16-byte loads in flight per lane (4 or 8); kS: wavefronts per row (1 .. 16)
 template <typename T, int kUnroll, int kS>
 __global__ void __launch_bounds__(1024)
 reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int K,
                    int32_t* __restrict__ out_ids, float* __restrict__ out_logit,
-                   float* __restrict__ out_lq, double* __restrict__ out_lse) {
+                   float* __restrict__ out_lq, double* __restrict__ out_lse, void* __restrict__ parts) {
   constexpr int VEC = Vec<T>::n;
   constexpr int CH = kWave * VEC;
   __shared__ float s_top[16 * kS];      // the waves' 16 largest lane maxima of the first group
@@ -324,8 +304,9 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   const int head = mis == 0 ? 0 : (VEC - mis < V ? VEC - mis : V);
   const int nv = (V - head) / VEC;
   const int nch = (nv + kWave - 1) / kWave;
-  const int c0 = (int)((int64_t)wave * nch / S);
-  const int c1 = (int)((int64_t)(wave + 1) * nch / S);
+  const int P = (int)gridDim.y, part = (int)blockIdx.y;   // a row may be cut into P parts, one workgroup each
+  const int c0 = (int)((int64_t)(part * S + wave) * nch / (P * S));
+  const int c1 = (int)((int64_t)(part * S + wave + 1) * nch / (P * S));
   const int v1 = c1 * kWave < nv ? c1 * kWave : nv;   // the segment's vectors are c0 kWave .. v1 - 1
 
   WaveState s;
@@ -336,7 +317,7 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   // wavefront, loaded ahead of its stream
   const int gap = nv * VEC;
   const auto edge_id = [head, gap](int l, int) { return l < head ? l : gap + l; };
-  const int edge = wave == S - 1 ? V - gap : 0;
+  const int edge = wave == S - 1 && part == P - 1 ? V - gap : 0;
   uint32_t edge_raw = 0u;
   if (lane < edge) edge_raw = raw_bits(rowp + edge_id(lane, 0));
 
@@ -466,14 +447,20 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   double sum = 0.0;
 #pragma unroll
   for (int w = 0; w < S; ++w) sum += ldexp(s_acc[w], (int)fmaxf(s_r[w] - R, -2000.f));
-  double corr = 0.0;
-  if (lane < K) {
-    const double approx = ldexp((double)term(s.lv, s.lr), (int)fmaxf(s.lr - R, -2000.f));
-    const double exact = exp2((double)s.lv * kLog2eD - (double)R);
-    corr = exact - approx;
+  sum = corrected_sum(sum, R, s.lv, s.lr, K, lane);
+  if (P > 1) {                             // a part's result, merged by the expansion
+    const PartRow pr = part_row(parts, row, K, P);
+    if (lane < K) {
+      pr.key[part * K + lane] = order_key(s.lv, s.lid);
+      pr.v[part * K + lane] = s.lv;
+    }
+    if (lane == 0) {
+      pr.sum[part] = sum;
+      pr.r[part] = R;
+    }
+    return;
   }
-  corr = xp::rl_d(xp::wave_incl_scan(corr), kWave - 1);
-  const double lse = (double)R * kLn2D + log(sum + corr);
+  const double lse = lse_of(sum, R);
   if (lane < K) {
     const int64_t o = row * K + lane;
     out_ids[o] = s.lid;
@@ -483,10 +470,34 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   if (lane == 0) out_lse[row] = lse;
 }
 
+// The parts of a split reduction merged by a kernel of its own, a wavefront a row, before the expansions whose
+// prologue does not (about 4 us, still less than the split saves).
+constexpr int kMergeRows = 4;
+__global__ void __launch_bounds__(kMergeRows * kWave) merge_kernel(MergeIn mg, int64_t rows, int K) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t row = (int64_t)blockIdx.x * kMergeRows + threadIdx.x / kWave;
+  if (row >= rows) return;
+  PartRegs m;
+  m.load(part_row(mg.parts, row, K, mg.split), K, mg.split, lane);
+  float v, R;
+  int id;
+  double sum;
+  merge_list(m, mg.split * K, lane, v, id);
+  merge_sum(m, mg.split, sum, R);
+  const double lse = lse_of(sum, R);
+  if (lane < K) {
+    mg.ids[row * K + lane] = id;
+    mg.logit[row * K + lane] = v;
+    if (mg.lq) mg.lq[row * K + lane] = (float)((double)v - lse);
+  }
+  if (lane == 0) mg.lse[row] = lse;
+}
+
 template <typename T, int U, int S>
 void launch_s(const ReduceArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL((reduce_topk_kernel<T, U, S>), dim3((unsigned)a.rows), dim3((unsigned)(kWave * S)), 0, stream,
-                     static_cast<const T*>(a.logits), a.row_stride, a.V, a.K, a.ids, a.logit, a.lq, a.lse);
+  hipLaunchKernelGGL((reduce_topk_kernel<T, U, S>), dim3((unsigned)a.rows, (unsigned)a.split),
+                     dim3((unsigned)(kWave * S)), 0, stream, static_cast<const T*>(a.logits), a.row_stride, a.V, a.K,
+                     a.ids, a.logit, a.lq, a.lse, a.parts);
 }
 
 template <typename T, int U>
@@ -509,31 +520,44 @@ hipError_t launch_t(const ReduceArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-// Launch shape.  The stream keeps HBM busy when about 32 MiB of loads are in
-// flight across the chip (resident waves x loads per lane x 1 KiB), and a row
-// split over fewer waves pays less for the start of each segment and for the
-// final merge.  Large batches: one wave per row, 8 loads in flight for bf16
-// (its kernel then holds 4 waves per SIMD, 4096 on the chip) and 4 for fp32
-// (8 per SIMD).  Batches of at most 4096 rows: 8 loads in flight, and the
-// fewest waves per row that still put 4096 waves on the chip at once.
-ReduceShape reduce_default_shape(int64_t rows, int32_t V, caddtree_dtype_t dtype) {
+// Launch shape, from sweeps of the shapes over 16 .. 22400 rows of 3000 .. 151936 logits (times in us).
+// - Large batches: one wave per row, 8 loads in flight (8192 rows of 151936 fp32: 728, with 4 loads 735), but 4
+//   from 4097 to 8191 rows, which then all fit on the chip (6400 rows of 151936 fp32: 582 against 595).
+// - Up to 4096 rows: the most waves per row, up to 8, that keep 4096 waves on the chip at once and leave a wave 3
+//   chunks (64 rows of 16 chunks: 1 wave 19.0, 2 waves 15.5, 4 waves 14.7; 128 rows of 63: 32.1, 25.5, 20.0, and
+//   8 waves 17.6).  16 waves are no better at any size (16 rows of 297 chunks 17.1, with 8 waves 16.6; 512
+//   rows 37.1 and 28.7).  fp32 rows of 4 waves and more on a full chip take 4 loads (1024 rows of 32000: 23.0
+//   against 24.5).
+// - So few rows that compute units are left idle, where there is memory for partial results: up to 4 parts per
+//   row, at most a compute unit's worth of parts each, and 4 chunks a wave (a build of 16 rows of 297 chunks:
+//   25.6, in two parts 23.1, in four 20.9, in eight 22.9, since the merge grows with the parts; 128 rows: 28.1,
+//   24.6, 26.1; 192 rows: 27.8, 30.2; 8 rows of 125 chunks: 16.0, 15.9, 15.7).
+ReduceShape reduce_default_shape(int64_t rows, int32_t V, int32_t K, caddtree_dtype_t dtype, bool may_split) {
   const int CH = kWave * (dtype == CADDTREE_BF16 ? 8 : 4);
   const int nch = (V + CH - 1) / CH;
-  ReduceShape sh{1, 4};
-  if (rows >= 8192) {
-    sh.unroll = dtype == CADDTREE_BF16 ? 8 : 4;
-  } else if (rows > 4096) {
-    sh.unroll = 4;
-  } else {
-    sh.unroll = 8;
-    while (sh.waves < 16 && rows * sh.waves * 2 <= 4096 && nch / (2 * sh.waves) >= 16) sh.waves *= 2;
+  ReduceShape sh{1, 8, 1};
+  if (rows > 4096) {
+    sh.unroll = rows >= 8192 ? 8 : 4;
+    return sh;
   }
+  while (sh.waves < 8 && rows * sh.waves * 2 <= 4096 && nch / (2 * sh.waves) >= 3) sh.waves *= 2;
+  if (dtype == CADDTREE_F32 && sh.waves >= 4 && rows >= 1024) sh.unroll = 4;
+  while (may_split && sh.split < 4 && rows * sh.split * 2 <= 256 && 2 * sh.split * K <= kWave &&
+         nch / (2 * sh.split * sh.waves) >= 4)
+    sh.split *= 2;
   return sh;
 }
 
 hipError_t launch_reduce_topk(const ReduceArgs& a, caddtree_dtype_t dtype, hipStream_t stream) {
   if (a.rows == 0) return hipSuccess;
   return dtype == CADDTREE_BF16 ? launch_t<uint16_t>(a, stream) : launch_t<float>(a, stream);
+}
+
+hipError_t launch_merge(const MergeIn& mg, int64_t rows, int32_t K, hipStream_t stream) {
+  if (rows == 0) return hipSuccess;
+  hipLaunchKernelGGL(merge_kernel, dim3((unsigned)((rows + kMergeRows - 1) / kMergeRows)), dim3(kMergeRows * kWave), 0,
+                     stream, mg, rows, K);
+  return hipGetLastError();
 }
 
 }  // namespace caddtree

@@ -1080,3 +1080,43 @@ def test_k1_first_group_threshold(dtype, waves, K, monkeypatch):
                 m = xd[b, i].max()
                 lse = m + np.log(np.exp(xd[b, i] - m).sum())
                 assert abs(h["lse"][b, i] - lse) <= 1e-7, (V, b, i)
+
+
+@pytest.mark.parametrize("name,kw,split", [
+    ("c1", dict(V=70001, B=3), 2),
+    ("c1", dict(V=30011, B=3), 8),                            # P K = 64 candidates
+    ("c1", dict(V=20, B=3, cap=30), 4),                       # parts without an element
+    ("c4", dict(V=9001, B=2), 4),                             # L = 32: four rows a wavefront, P K = 64
+    ("c4", dict(V=9001, B=2, L=9, K=5), 8),
+    ("c3", dict(V=9000, B=2), 2),
+    ("c1", dict(V=9000, B=2, cap=600, fixed=True), 4),         # several-wavefront expansion: the merge kernel
+])
+def test_split_rows(name, kw, split, monkeypatch):
+    """Rows cut into parts whose results the expansion's prologue (or the merge kernel) merges: the oracle's
+    top-K table and trees, with a workspace for the parts and, of one workgroup a row, without."""
+    import torch
+    monkeypatch.setenv("CADDTREE_K1_SPLIT", str(split))
+    cfg = synth.get_config(name).replace(**kw)
+    rounds = list(range(cfg.B))
+    h, rs = _parity_batch(cfg, rounds, pos_offset=3)
+    plan = make_plan(cfg)
+    monkeypatch.delenv("CADDTREE_K1_SPLIT")
+    whole = make_plan(cfg)
+    _, x, _ = _guard.guarded_batch(cfg, rounds, pos_offset=3)
+    lg = torch_logits(cfg, x)
+    up = lambda n: (n + 255) // 256 * 256
+    room = 2 * up(cfg.B * cfg.L * cfg.K * 4) + up(cfg.B * cfg.L * 8)                         # the table alone
+    assert room < plan.workspace_bytes(cfg.B)
+    out = plan.new_outputs(cfg.B)
+    plan.build(lg, out, pos_offset=3, workspace=torch.empty(room, dtype=torch.uint8, device="cuda"))
+    ref = whole.new_outputs(cfg.B, topk=True)
+    whole.build(lg, ref, pos_offset=3)
+    noalloc = plan.new_outputs(cfg.B)
+    plan.build_noalloc(lg, noalloc, pos_offset=3)
+    torch.cuda.synchronize()
+    for got in (host(out), host(ref), host(noalloc)):
+        assert np.array_equal(got["n_star"], h["n_star"])
+        for i, n in enumerate(h["n_star"]):
+            for k in ("token_ids", "parent", "depth", "pos_ids"):
+                assert np.array_equal(got[k][i, :n], h[k][i, :n]), (i, k)
+            np.testing.assert_allclose(got["path_prob"][i, :n], h["path_prob"][i, :n], rtol=1e-5)
