@@ -6,8 +6,8 @@
 // one SIMD of its CU busy and leaves the rest idle; here 8 or 16 wavefronts
 // share each pass over a level or over the set.
 //
-// The steps are those of the one-wavefront kernel (expand_level.hip): build
-// T(tau) level by level, raise tau in place when a level overflows the set,
+// The steps are those of the one-wavefront kernel (expand_level.hip), from a
+// first threshold found by counting nodes (count_tau): build T(tau) level by level, raise tau in place when a level overflows the set,
 // lower it when the set is too small, find the stop by a histogram of sigma,
 // then lay the kept nodes out in breadth-first order.  Each pass is split into
 // 64-node chunks, chunk k going to wavefront k mod NW; the steps that need the
@@ -202,6 +202,110 @@ __device__ double wide_raise(const Lds& s, WideShared& x, int& la, int& lb, int 
   return t2;
 }
 
+// The threshold that about `need` nodes reach, from a count of the nodes per value of sigma: sigma is a sum of
+// one log-probability per depth, so the nodes of depth d per value are those of depth d - 1 shifted by each
+// rank's log-probability, added up.  Counted in kCountBins bins of `range` nats in all (a rank's shift is
+// rounded to a bin, an error of a fraction of a bin that grows with the root of the depth).  Returns NaN when
+// fewer nodes than wanted lie within the range.  Called by every thread; one barrier a depth.
+//
+// A first threshold a fixed distance below the top node let a level overflow the set again and again, and every
+// in-place raise (a histogram of the set, a compaction, the level built anew) costs as much as several levels.
+// With the count a round is built once, without a raise (sets of 4400 nodes for trees of 4096, 1110 for 1024):
+// 64 rounds of 4096 nodes (L = 32, K = 16) 95.5 -> 62 us, of 1024 nodes (L = 16, K = 8) 42 -> 37.5.  One read at
+// a time and every depth counted, the count took 53 us of the first; four reads in flight and no bin below the
+// one where the count is reached, about 8.
+constexpr int kCountBins = 1024;
+
+// The first bin at which the running count reaches `want` (kCountBins: none), the same in every thread; t is
+// LDS for the counts, which an earlier call's readers are done with (a barrier since).
+template <int NW>
+__device__ int count_reached(float* t, const float (&total)[kCountBins / (NW * kW)], double want, int lane, int tid) {
+#pragma unroll
+  for (int u = 0; u < kCountBins / (NW * kW); ++u) t[tid + u * (NW * kW)] = total[u];
+  __syncthreads();
+  const float* own = t + 16 * lane;                      // lane l: bins 16 l .. 16 l + 15
+  float v[16];
+  double sum = 0.0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) { v[j] = own[j]; sum += (double)v[j]; }
+  double c = wave_incl_scan(sum);
+  const unsigned long long m = __ballot(c >= want);
+  if (m == 0) return kCountBins;
+  const int l = __builtin_ctzll(m);
+  int j = 15;                                            // the lane's last bin reaches it: walk back
+#pragma unroll
+  for (int k = 15; k > 0; --k) {
+    c -= (double)v[k];
+    j = c >= want ? k - 1 : j;
+  }
+  return 16 * l + __builtin_amdgcn_readlane(j, l);
+}
+
+template <int NW>
+__device__ double count_tau(const Lds& s, const WideShared& x, int L, int K, double range, double want, int lane,
+                            int tid) {
+  constexpr int kPer = kCountBins / (NW * kW);           // bins a thread: tid, tid + NW 64, ..
+  static_assert(kPer * NW * kW == kCountBins, "every bin has a thread");
+  float* buf = reinterpret_cast<float*>(s.dl);           // two depths' counts (free before the set is selected)
+  const double inv_w = (double)kCountBins / range;
+  float total[kPer];
+  __syncthreads();                                       // an earlier count's readers are done
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    total[u] = 0.f;
+    buf[tid + u * (NW * kW)] = tid + u * (NW * kW) == 0 ? 1.f : 0.f;   // the root, at sigma 0
+  }
+  __syncthreads();
+  int cur = 0;
+  int lim = kCountBins - 1;                              // the threshold lies in this bin or above
+  for (int d = 0; d < L; ++d) {
+    const double lq = lane < K ? (double)s.tl[d * K + (lane < K ? lane : 0)] - (x.A[d + 1] - x.A[d]) : -INFINITY;
+    const int q = (int)fmax(fmin(0.5 - lq * inv_w, (double)kCountBins), 0.0);   // (NaN: out of range)
+    const int nr = __popcll(__ballot(q < kCountBins));   // ranks within the range (they fall with the rank)
+    const float* from = buf + cur * kCountBins;
+    float h[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) h[u] = 0.f;
+    for (int r0 = 0; r0 < nr; r0 += 4) {                 // four reads in flight; q is out of range past rank nr
+      float v[4][kPer];
+      bool in[4][kPer];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int qr = __builtin_amdgcn_readlane(q, r0 + r);
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+          const int at = tid + u * (NW * kW) - qr;
+          in[r][u] = at >= 0;
+          v[r][u] = from[at > 0 ? at : 0];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) h[u] += in[r][u] ? v[r][u] : 0.f;
+    }
+    cur ^= 1;
+    bool some = false;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      h[u] = tid + u * (NW * kW) <= lim ? h[u] : 0.f;
+      buf[cur * kCountBins + tid + u * (NW * kW)] = h[u];
+      total[u] += h[u];
+      some = some || h[u] > 0.f;
+    }
+    if (__syncthreads_or(some ? 1 : 0) == 0) break;      // no deeper node lies within the range
+    // once the count is reached, what lies below that bin no longer matters: the count's depth is then the
+    // tree's and not that of the whole range
+    if (d == 2 || d == 4 || d == 7) {
+      const int at = count_reached<NW>(reinterpret_cast<float*>(s.sl), total, want, lane, tid);
+      lim = at < lim ? at : lim;
+    }
+  }
+  __syncthreads();
+  const int at = count_reached<NW>(reinterpret_cast<float*>(s.sl), total, want, lane, tid);
+  return at < kCountBins ? -(double)(at + 1) / inv_w : NAN;
+}
+
 // Where the stop falls in a set of more than 128 nodes: the histogram search of stop_hist, with
 // the histograms and the classification passes split over the wavefronts and the stop inside
 // its bin found by wavefront 0.  Returns false (fallback) when no bin of at most 64 nodes holds
@@ -355,7 +459,13 @@ expand_wide_kernel(const int32_t* __restrict__ topk_ids, const float* __restrict
   const double top = pmin(0.0 + (double)s.tl[0] - A1, 0.0);   // the first node to pop
   int need = cap;                            // the tree keeps cap nodes before any stop test
   bool tight = true;
-  double tau = fmin(top - drop_fixed(need), top);
+  // the counted threshold, with a margin for the bins' rounding; a fixed distance below the top node where
+  // the count's ranges hold too few nodes
+  double tau = count_tau<NW>(s, x, L, K, 16.0, 1.06 * (double)need + 8.0, lane, tid);
+  if (!(tau < 0.0)) tau = count_tau<NW>(s, x, L, K, 48.0, 1.12 * (double)need + 8.0, lane, tid);
+  bool counted = tau < 0.0;
+  if (!counted) tau = top - drop_fixed(need);
+  tau = fmin(tau, top);
   const StopTest tst{cap, fixed, fixed ? 0 : 1, c0, nullptr};
 
   int n = 0, ns = 0;
@@ -450,7 +560,9 @@ expand_wide_kernel(const int32_t* __restrict__ topk_ids, const float* __restrict
     const bool cut = x.cut != 0 || dropped;
     ns = lb;
     if (cut && ns < need && ns < cap) {     // too few nodes to hold the stop: lower tau without selecting
-      tau -= fmax(log(4.0 * (double)need / (double)(ns > 0 ? ns : 1)), 1.0);
+      const double few = log((double)need / (double)(ns > 0 ? ns : 1));
+      tau -= counted && few < 0.5 ? 1.5 * few + 0.05 : fmax(few + log(4.0), 1.0);
+      counted = false;
       continue;
     }
 

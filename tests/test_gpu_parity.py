@@ -1120,3 +1120,30 @@ def test_split_rows(name, kw, split, monkeypatch):
             for k in ("token_ids", "parent", "depth", "pos_ids"):
                 assert np.array_equal(got[k][i, :n], h[k][i, :n]), (i, k)
             np.testing.assert_allclose(got["path_prob"][i, :n], h["path_prob"][i, :n], rtol=1e-5)
+
+
+@pytest.mark.parametrize("scale", [0.02, 1.0, 12.0])
+@pytest.mark.parametrize("L,K,cap", [(9, 2, 512), (12, 2, 700), (4, 16, 1500), (16, 8, 1024), (32, 16, 4096)])
+def test_wide_counted_threshold(scale, L, K, cap, monkeypatch):
+    """The several-wavefront kernel's counted first threshold over flat, ordinary and sharp rows, trees of half
+    the nodes there are (512 of 1022 for L = 9) and of the largest cap: the one-wavefront kernel's trees."""
+    import torch
+    rng = np.random.default_rng(3)
+    B, V = 5, 600
+    x = (scale * rng.standard_normal((B, L, V))).astype(np.float32)
+    x[1] = np.round(x[1] * 2.0 / scale) * scale / 2.0                    # ties
+    x[2, L // 2] = -np.inf                                              # a position of K certain tokens
+    x[2, L // 2, :K] = 0.0
+    cfg = synth.get_config("c4").replace(B=B, L=L, V=V, K=K, cap=cap, fixed=True, dtype="f32")
+    lg = torch_logits(cfg, x)
+    outs = {}
+    for mode in ("auto", "level"):
+        if mode == "level":
+            monkeypatch.setenv("CADDTREE_EXPAND", "level")
+        outs[mode] = host(run_build(make_plan(cfg), lg))
+    a, b = outs["auto"], outs["level"]
+    assert np.array_equal(a["n_star"], b["n_star"])
+    assert (a["n_star"] == min(cap, sum(K ** d for d in range(1, L + 1)))).all()
+    for i, n in enumerate(a["n_star"]):
+        for k in ("token_ids", "parent", "depth", "pos_ids", "path_prob"):
+            assert np.array_equal(a[k][i, :n], b[k][i, :n]), (i, k)
