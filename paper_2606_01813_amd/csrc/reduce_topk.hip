@@ -7,7 +7,7 @@
 // before and after it (rows of a vocabulary or a stride that is no multiple of 16
 // bytes start anywhere) are one more step of the last wavefront, one element a lane.
 // (Element loads for every row off a 16-byte boundary took 181 us for 48 x 15 rows of
-// 100003 bf16 logits; the vectors and the edge step take 40 us.)
+// 100003 bf16 logits; the vectors and the edge step 40, and 33 since the row-wide threshold.)
 // A wavefront streams 16-byte loads (8 bf16 or 4 fp32 per lane, 1 KiB per wave per load) and
 // keeps, per lane, an fp64 sum of 2^(x log2 e - r) where r is a wave-uniform
 // integer exponent, a little below the running maximum's, that only grows: when it moves, the sums are rescaled by an
