@@ -44,23 +44,33 @@ constexpr int kWave = 64;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Streaming 16-byte loads of a wavefront's segment, with the non-temporal hint (each byte of the logits is
-// read once).  Buffer loads: the segment's base and the chunk's offset are scalars and the lane's offset never
-// changes, so a load needs no vector address arithmetic, and a load past the segment's end returns zeros
-// without touching memory, so the ring needs no branch or clamp at the end of a segment.
+// read once).  Buffer loads: the segment's base and size are scalars and the lane's offset never changes, so a
+// load needs no vector address arithmetic, and a load past the segment's end returns zeros without touching
+// memory, so the ring needs no branch or clamp at the end of a segment.  The hardware holds the sum of the lane's
+// offset and the instruction's (12 bits) against the size; the scalar offset is no part of that check, so it
+// stays 0 and a group of eight loads takes two descriptors, 4 KiB apart.
 constexpr int kNonTemporal = 2;                 // the nt bit of a buffer load's cache policy
+constexpr int kSpan = 4;                        // loads of 1 KiB that the instruction's offset reaches
 struct Segment {
   const char* base;                             // the next group's first vector (wave-uniform)
   int64_t left;                                 // bytes from there to the segment's end
-  // the U loads of a group: vector u * kWave + lane
-  __device__ __forceinline__ auto rsrc() const {
-    const int64_t cut = left < 0 ? 0 : (left < (1 << 30) ? left : (1 << 30));   // a group is at most 8 KiB
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (int)cut, 0x00027000);
+  // the bytes from `at` on
+  __device__ __forceinline__ auto rsrc(int at) const {
+    const int64_t n = left - at;
+    const int64_t cut = n < 0 ? 0 : (n < (1 << 30) ? n : (1 << 30));   // a group is at most 8 KiB
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base) + at, 0, (int)cut, 0x00027000);
   }
 };
 template <typename R>
-__device__ __forceinline__ uint4 stream_load(R rsrc, int lane_off, int off) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off, off, kNonTemporal);
+__device__ __forceinline__ uint4 span_load(R rsrc, int& lane_off, int k) {
+  asm volatile("" : "+v"(lane_off));            // (no register is kept for its sums with the loads' places)
+  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off + k * (kWave * 16), 0, kNonTemporal);
   return make_uint4(v.x, v.y, v.z, v.w);
+}
+// load u of a group (u is known at compile time): vector u kWave + lane; lo and hi: the group's descriptors
+template <typename R>
+__device__ __forceinline__ uint4 stream_load(R lo, R hi, int& lane_off, int u) {
+  return u < kSpan ? span_load(lo, lane_off, u) : span_load(hi, lane_off, u - kSpan);
 }
 
 template <typename T> struct Vec;
@@ -321,15 +331,15 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   uint32_t edge_raw = 0u;
   if (lane < edge) edge_raw = raw_bits(rowp + edge_id(lane, 0));
 
-  const int lane_off = lane * 16;
+  int lane_off = lane * 16;
   Segment seg{reinterpret_cast<const char*>(rowp + head) + (int64_t)c0 * (kWave * 16),
               (int64_t)(v1 - c0 * kWave) * 16};
   int c = c0;
   uint4 q[kUnroll];
   {
-    const auto r = seg.rsrc();
+    const auto lo = seg.rsrc(0), hi = seg.rsrc(kSpan * kWave * 16);
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) q[u] = stream_load(r, lane_off, u * (kWave * 16));
+    for (int u = 0; u < kUnroll; ++u) q[u] = stream_load(lo, hi, lane_off, u);
   }
   // The first group (all of a short segment) sets the reference exponent and the initial threshold: the
   // K-th largest over the row's wavefronts of each lane's maximum, so that K elements reach it.  Whatever
@@ -377,12 +387,12 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
     for (; c + kUnroll < c1; c += kUnroll) {
       seg.base += kUnroll * kWave * 16;
       seg.left -= kUnroll * kWave * 16;
-      const auto r = seg.rsrc();
+      const auto lo = seg.rsrc(0), hi = seg.rsrc(kSpan * kWave * 16);
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         float x[VEC];
         unpack(q[u], x);
-        q[u] = stream_load(r, lane_off, u * (kWave * 16));
+        q[u] = stream_load(lo, hi, lane_off, u);
         chunk<VEC>(s, x, true, head + (c + u) * CH, K, lane);
       }
     }
