@@ -115,6 +115,8 @@ caddtree::ReduceShape reduce_shape(const caddtree_plan* p, int64_t rows, bool ma
 // The parts of a row in a build of B rounds with `bytes` of workspace past the top-K table's (1: not split),
 // and the bytes they take.
 int32_t build_split(const caddtree_plan* p, int64_t B, size_t bytes, size_t* need) {
+  *need = 0;
+  if (B > INT32_MAX / p->L) return 1;          // more rows than a build takes (a size query may ask)
   const int64_t rows = B * p->L;
   const int32_t split = p->k1_split > 0 ? p->k1_split : reduce_shape(p, rows, true).split;
   *need = split > 1 ? (size_t)rows * (size_t)caddtree::split_row_bytes(p->K, split) : 0;

@@ -129,9 +129,40 @@ int main() {
 }
 """
 
+# Workspace sizes, of plans made here without a GPU (the plan's definition comes with api.cpp itself)
+SIZES = r"""
+#include "api.cpp"
 
-@pytest.fixture(scope="module")
-def sanitized(tmp_path_factory):
+static int fails = 0;
+#define EXPECT(c) do { if (!(c)) { std::printf("FAILED line %d: %s\n", __LINE__, #c); ++fails; } } while (0)
+
+static size_t table(const caddtree_plan& p, int64_t B) {
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  const size_t rows = (size_t)B * (size_t)p.L;
+  return 2 * up(rows * p.K * 4) + up(rows * 8);
+}
+
+int main() {
+  for (int L : {1, 3, 4, 8, 16, 32})
+    for (int K : {1, 4, 8, 16})
+      for (int64_t V : {(int64_t)16, (int64_t)4096, (int64_t)32000, (int64_t)151936})
+        for (int dt : {CADDTREE_F32, CADDTREE_BF16}) {
+          caddtree_plan p = {};
+          p.L = L; p.K = K; p.V = V; p.cap = 64; p.dtype = (caddtree_dtype_t)dt; p.num_cu = 256;
+          // batches that no build takes: the table's size alone, whatever their product with L
+          for (int64_t B : {(int64_t)INT32_MAX / L + 1, (int64_t)1 << 40, INT64_MAX / 32 + 1, INT64_MAX / 3 * 2,
+                            INT64_MAX})
+            EXPECT(caddtree_workspace_bytes(&p, B) == table(p, B));
+          for (int64_t B : {(int64_t)1, (int64_t)8, (int64_t)129, (int64_t)100000})
+            EXPECT(caddtree_workspace_bytes(&p, B) >= table(p, B));
+        }
+  std::printf("sizes done, %d failures\n", fails);
+  return fails == 0 ? 0 : 1;
+}
+"""
+
+
+def _sanitized_program(tmp_path_factory, driver, sources):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("g++ is not available")
@@ -142,11 +173,11 @@ def sanitized(tmp_path_factory):
     if missing:
         pytest.fail(f"build the library first (python -m paper_2606_01813_amd._build): {missing}")
     d = tmp_path_factory.mktemp("asan")
-    (d / "driver.cpp").write_text(DRIVER)
+    (d / "driver.cpp").write_text(driver)
     inc = ["-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", "/opt/rocm/include"]
     san = ["-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-fno-omit-frame-pointer"]
     built = []
-    for src in ("api.cpp", "costfit.cpp", str(d / "driver.cpp")):
+    for src in sources + (str(d / "driver.cpp"),):
         path = src if os.path.isabs(src) else os.path.join(CSRC, src)
         obj = str(d / (os.path.basename(src) + ".o"))
         cmd = [gxx, "-std=c++17", "-O1", "-g", "-fPIC", "-Wall"] + san + inc + ["-c", path, "-o", obj]
@@ -161,11 +192,24 @@ def sanitized(tmp_path_factory):
     return exe
 
 
-def test_host_code_is_clean_under_asan_and_ubsan(sanitized):
+def _run_clean(exe):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1:abort_on_error=0",
                UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1", HIP_VISIBLE_DEVICES="")
-    r = subprocess.run([sanitized], capture_output=True, text=True, timeout=300, env=env)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=env)
     out = r.stdout + r.stderr
     assert "ERROR: AddressSanitizer" not in out and "runtime error" not in out, out[-4000:]
     assert r.returncode == 0, out[-4000:]
-    assert "host checks done, 0 failures" in r.stdout
+    return r.stdout
+
+
+@pytest.fixture(scope="module")
+def sanitized(tmp_path_factory):
+    return _sanitized_program(tmp_path_factory, DRIVER, ("api.cpp", "costfit.cpp"))
+
+
+def test_host_code_is_clean_under_asan_and_ubsan(sanitized):
+    assert "host checks done, 0 failures" in _run_clean(sanitized)
+
+
+def test_workspace_sizes_of_any_batch(tmp_path_factory):
+    assert "sizes done, 0 failures" in _run_clean(_sanitized_program(tmp_path_factory, SIZES, ("costfit.cpp",)))
