@@ -122,10 +122,11 @@ caddtree_status_t caddtree_plan_create(const caddtree_config_t* cfg, caddtree_pl
 /* Frees the plan (NULL is a no-op).  The caller ensures no enqueued work still uses it. */
 void caddtree_plan_destroy(caddtree_plan_t plan);
 
-/* Device workspace caddtree_build uses for B rounds: the top-K table when the
- * caller does not ask for it, and for a few rounds the partial results of rows
- * that several workgroups reduce (a workspace that holds the table alone is
- * accepted; such a call reduces a row in one workgroup).  256-byte alignment is
+/* Device workspace caddtree_build uses for up to B rounds: the top-K table when
+ * the caller does not ask for it, and for a few rounds the partial results of
+ * rows that several workgroups reduce (a workspace that holds the table alone is
+ * accepted; such a call reduces a row in one workgroup, and the last bits of its
+ * normalisers may differ).  It never falls as B grows.  256-byte alignment is
  * required. */
 size_t caddtree_workspace_bytes(caddtree_plan_t plan, int64_t B);
 

@@ -424,10 +424,18 @@ void caddtree_plan_destroy(caddtree_plan_t p) {
 
 size_t caddtree_workspace_bytes(caddtree_plan_t p, int64_t B) {
   if (p == nullptr || B <= 0) return 0;
-  TopkBuffers tb;
-  size_t split = 0;
-  build_split(p, B, SIZE_MAX, &split);
-  return topk_workspace(p, B, nullptr, nullptr, &tb) + align256(split);
+  const auto used = [p](int64_t b) {
+    TopkBuffers tb;
+    size_t split = 0;
+    build_split(p, b, SIZE_MAX, &split);
+    return topk_workspace(p, b, nullptr, nullptr, &tb) + align256(split);
+  };
+  // A few rounds with their rows in parts use more than somewhat more rounds with theirs whole, so this is the
+  // most that any batch up to B uses: a workspace sized for the largest batch serves every smaller one as one of
+  // its own.  (Only batches of fewer rows than compute units are cut.)
+  size_t most = used(B);
+  for (int64_t b = std::min<int64_t>(B, p->num_cu / p->L); b > 0; --b) most = std::max(most, used(b));
+  return most;
 }
 
 caddtree_status_t caddtree_reduce_topk(caddtree_plan_t p, const void* logits, int64_t B, int64_t row_stride,

@@ -149,12 +149,19 @@ int main() {
         for (int dt : {CADDTREE_F32, CADDTREE_BF16}) {
           caddtree_plan p = {};
           p.L = L; p.K = K; p.V = V; p.cap = 64; p.dtype = (caddtree_dtype_t)dt; p.num_cu = 256;
-          // batches that no build takes: the table's size alone, whatever their product with L
+          // a workspace for the largest batch serves every smaller one, parts included
+          size_t most = 0;
+          for (int64_t B = 1; B <= 300; ++B) {
+            size_t parts = 0;
+            build_split(&p, B, SIZE_MAX, &parts);
+            most = std::max(most, table(p, B) + (parts + 255) / 256 * 256);
+            EXPECT(caddtree_workspace_bytes(&p, B) == most);
+          }
+          // batches that no build takes: no parts, whatever their product with L
           for (int64_t B : {(int64_t)INT32_MAX / L + 1, (int64_t)1 << 40, INT64_MAX / 32 + 1, INT64_MAX / 3 * 2,
                             INT64_MAX})
-            EXPECT(caddtree_workspace_bytes(&p, B) == table(p, B));
-          for (int64_t B : {(int64_t)1, (int64_t)8, (int64_t)129, (int64_t)100000})
-            EXPECT(caddtree_workspace_bytes(&p, B) >= table(p, B));
+            EXPECT(caddtree_workspace_bytes(&p, B) >= table(p, B) &&
+                   caddtree_workspace_bytes(&p, B) <= std::max(most, table(p, B)));
         }
   std::printf("sizes done, %d failures\n", fails);
   return fails == 0 ? 0 : 1;
