@@ -116,7 +116,8 @@ class Plan:
     """An immutable CaDDTree plan (shape limits, dtype, mask format, cost model).
 
     Each call goes to the native binding first, which checks the tensors and calls the library; what it
-    cannot vouch for comes back as None and takes the Python checks here, which raise what is wrong."""
+    cannot vouch for comes back as None and takes the Python checks here, which raise what is wrong.  Where
+    the native binding was not built every call takes them, some 15 us more of host time a build."""
 
     _fast = None            # the native calls' view of the plan
 

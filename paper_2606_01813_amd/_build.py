@@ -1,4 +1,5 @@
-"""Builds libcaddtree.so (gfx950) in-tree with hipcc.
+"""Builds libcaddtree.so (gfx950) in-tree with hipcc, and the Python binding's native calls where torch's
+and Python's headers are there (the library needs neither).
 
 Every HIP translation unit is compiled with packed fp32 instructions disabled
 (``-target-feature -packed-fp32-ops``).
@@ -44,7 +45,17 @@ def common_flags():
 
 
 def torch_dir() -> str:
-    return os.path.dirname(importlib.util.find_spec("torch").origin)
+    spec = importlib.util.find_spec("torch")
+    return "" if spec is None else os.path.dirname(spec.origin)
+
+
+def binding_lacks() -> str:
+    """What the binding's native calls cannot be built without and is not there ("" if all is)."""
+    need = [os.path.join(torch_dir(), "include", "torch", "csrc", "autograd", "python_variable.h"),
+            os.path.join(sysconfig.get_paths()["include"], "Python.h")]
+    if not torch_dir():
+        return "torch"
+    return ", ".join(f for f in need if not os.path.exists(f))
 
 
 def binding_flags():
@@ -82,13 +93,19 @@ def _link(objs, out: str, verbose: bool, libs=()) -> None:
 def build(verbose: bool = False) -> str:
     obj_dir = os.path.join(PKG, "_build")
     os.makedirs(obj_dir, exist_ok=True)
-    srcs = SOURCES + PROBE_SOURCES + [BINDING_SOURCE]
+    lacks = binding_lacks()
+    srcs = SOURCES + PROBE_SOURCES + ([] if lacks else [BINDING_SOURCE])
     with cf.ThreadPoolExecutor(max_workers=len(srcs)) as ex:
-        objs = dict(zip(srcs, ex.map(lambda s: _compile(s, obj_dir, verbose), srcs)))
-    _link([objs[s] for s in SOURCES], LIB, verbose)
-    _link([objs[s] for s in PROBE_SOURCES], PROBE_LIB, verbose)
-    _link([objs[BINDING_SOURCE]], BINDING, verbose,
-          ["-L" + os.path.join(torch_dir(), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"])
+        objs = {s: ex.submit(_compile, s, obj_dir, verbose) for s in srcs}
+    _link([objs[s].result() for s in SOURCES], LIB, verbose)
+    _link([objs[s].result() for s in PROBE_SOURCES], PROBE_LIB, verbose)
+    if lacks:                # the Python path serves without it; none of another source may stay
+        print(f"the binding's native calls are not built: {lacks} not found", file=sys.stderr)
+        if os.path.exists(BINDING):
+            os.remove(BINDING)
+    else:
+        _link([objs[BINDING_SOURCE].result()], BINDING, verbose,
+              ["-L" + os.path.join(torch_dir(), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"])
     return LIB
 
 

@@ -113,12 +113,9 @@ _BINDING = None
 
 
 def binding():
-    """The native calls of the binding (csrc/binding.cpp)."""
+    """The native calls of the binding (csrc/binding.cpp); None where they were not built."""
     global _BINDING
-    if _BINDING is None:
-        path = os.path.join(_HERE, "_binding.so")
-        if not os.path.exists(path):
-            raise ImportError(f"{path} is missing: build the library first (python -m paper_2606_01813_amd._build)")
+    if _BINDING is None and os.path.exists(os.path.join(_HERE, "_binding.so")):
         import torch  # noqa: F401  (the module uses torch's libraries)
         from . import _binding
         _BINDING = _binding
@@ -126,7 +123,10 @@ def binding():
 
 
 def call_spec(lib_, handle: int, device: int, L: int, V: int, K: int, cap: int, dtype: str, mask: str):
-    """What the native calls need of a plan: its handle, the shapes of its tensors and the library's functions."""
+    """What the native calls need of a plan: its handle, the shapes of its tensors and the library's functions.
+    None where the native calls were not built."""
+    if binding() is None:
+        return None
     fns = (lib_.caddtree_build, lib_.caddtree_build_noalloc, lib_.caddtree_reduce_topk, lib_.caddtree_expand,
            lib_.caddtree_emit, lib_.caddtree_accept)
     return binding().spec(handle, device, L, V, K, cap, DTYPES[dtype], MASKS[mask],
