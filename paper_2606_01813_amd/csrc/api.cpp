@@ -8,7 +8,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
-#include <string>
 
 #include "internal.h"
 
@@ -41,21 +40,19 @@ struct caddtree_plan {
 
 namespace {
 
-thread_local std::string g_last_error;
+thread_local char g_last_error[512];   // (a string could throw out of a C function)
 
 caddtree_status_t fail(caddtree_status_t st, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 caddtree_status_t fail(caddtree_status_t st, const char* fmt, ...) {
-  char buf[512];
   va_list ap;
   va_start(ap, fmt);
-  vsnprintf(buf, sizeof(buf), fmt, ap);
+  vsnprintf(g_last_error, sizeof(g_last_error), fmt, ap);
   va_end(ap);
-  g_last_error = buf;
   return st;
 }
 
 caddtree_status_t ok() {
-  g_last_error.clear();
+  g_last_error[0] = '\0';
   return CADDTREE_OK;
 }
 
@@ -241,7 +238,7 @@ const char* caddtree_status_string(caddtree_status_t s) {
   return "unknown status";
 }
 
-const char* caddtree_last_error(void) { return g_last_error.c_str(); }
+const char* caddtree_last_error(void) { return g_last_error; }
 
 caddtree_status_t caddtree_plan_create(const caddtree_config_t* cfg, caddtree_plan_t* plan_out) {
   if (plan_out == nullptr) return fail(CADDTREE_E_INVALID, "plan_out is NULL");

@@ -186,6 +186,9 @@ T* as(void* p) { return static_cast<T*>(p); }
 
 const char* const kSpecName = "caddtree.spec";
 
+// an exception came out of the library's call, whose work may be enqueued already: not to be called again
+struct LibraryThrew {};
+
 template <typename F>
 PyObject* guarded(PyObject* const* args, Py_ssize_t nargs, Py_ssize_t want, F&& body) {
   if (nargs != want) {
@@ -197,6 +200,9 @@ PyObject* guarded(PyObject* const* args, Py_ssize_t nargs, Py_ssize_t want, F&& 
   int status = -1;
   try {
     status = body(*s);
+  } catch (const LibraryThrew&) {
+    PyErr_SetString(PyExc_RuntimeError, "the caddtree library threw an exception");
+    return nullptr;
   } catch (...) {          // a tensor that cannot be looked at this way
     status = -1;
   }
@@ -204,14 +210,19 @@ PyObject* guarded(PyObject* const* args, Py_ssize_t nargs, Py_ssize_t want, F&& 
   return PyLong_FromLong(status);
 }
 
-// the library's call without the interpreter's lock, as ctypes makes it
+// the library's call without the interpreter's lock, as ctypes makes it; the lock is back however the call ends
+struct Unlocked {
+  PyThreadState* const state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
 template <typename F>
 int unlocked(F&& f) {
-  int status;
-  Py_BEGIN_ALLOW_THREADS
-  status = (int)f();
-  Py_END_ALLOW_THREADS
-  return status;
+  try {
+    const Unlocked u;
+    return (int)f();
+  } catch (...) {
+    throw LibraryThrew();
+  }
 }
 
 void tree_fields(Call& c, PyObject* out, int64_t B, caddtree_outputs_t* o) {

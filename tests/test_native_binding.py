@@ -7,6 +7,10 @@ library's.
 """
 
 import ctypes
+import os
+import shutil
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -185,3 +189,32 @@ def test_native_calls_pass_what_the_python_path_passes(call, L, cap, mask, dtype
     if call not in ("reduce_topk", "expand", "accept"):
         s["out"] = object()
         both("no outputs")
+
+
+_THROWS = r"""
+import ctypes, sys
+import torch
+from paper_2606_01813_amd import _lib
+f = ctypes.cast(ctypes.CDLL(sys.argv[1]).throws, ctypes.c_void_p).value
+native = _lib.binding()
+spec = native.spec(0x10, -1, 2, 16, 2, 4, 0, 0, f, f, f, f, f, f)
+i32 = torch.zeros((1, 2, 2), dtype=torch.int32)
+try:
+    native.reduce_topk(spec, torch.zeros((1, 2, 16)), i32, torch.zeros((1, 2, 2)), torch.zeros((1, 2), dtype=torch.float64),
+                       None, 0)
+except RuntimeError as e:
+    print("raised", e, sum(range(1000)))
+"""
+
+
+def test_an_exception_out_of_the_library_is_raised_with_the_lock_held(tmp_path):
+    """Raised once, and not passed to the Python path, which would make the call again."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ is not available")
+    (tmp_path / "throws.cpp").write_text("#include <new>\nextern \"C\" int throws() { throw std::bad_alloc(); }\n")
+    so = str(tmp_path / "throws.so")
+    subprocess.run([gxx, "-shared", "-fPIC", "-o", so, str(tmp_path / "throws.cpp")], check=True)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(pkg.__file__)))
+    r = subprocess.run([sys.executable, "-c", _THROWS, so], capture_output=True, text=True, cwd=root, timeout=300)
+    assert r.returncode == 0 and "raised the caddtree library threw" in r.stdout, r.stdout + r.stderr
