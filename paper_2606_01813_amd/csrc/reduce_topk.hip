@@ -15,8 +15,8 @@
 // (two fmas), so the only per-term error is the hardware exp2.
 //
 // Top-K: the wave keeps a sorted list of 16 slots in lanes 0..15 of its first
-// DPP row.  An element is a candidate when it is >= the wave threshold (the
-// K-th slot, or an initial lower bound); the fast path is one compare of the
+// DPP row.  An element is a candidate when it reaches the wave threshold (an initial
+// lower bound, then the next value above the K-th slot's); the fast path is one compare of the
 // lane's chunk maximum per 8 elements, and the rare path inserts candidates one
 // at a time with a DPP row shift.  The initial bound is the K-th largest of the lanes' maxima over
 // the first chunks of all of the row's wavefronts, which is <= the K-th largest element, so no
@@ -165,13 +165,22 @@ struct WaveState {
   double acc;     // per lane
   float r;        // wave-uniform reference exponent (integral value)
   float mx;       // wave-uniform running maximum
-  float thr;      // wave-uniform candidate threshold
-  int thr_id;
+  float thr;      // wave-uniform: an element still to come is a candidate if it reaches this
   float lv;       // list slot (lanes 0..15): value, id, exponent at insertion
   int lid;
   float lr;
 };
 
+// the least value above v (+inf: NaN, which no value reaches)
+__device__ __forceinline__ float next_up(float v) {
+  const int b = __float_as_int(v);
+  return __int_as_float(v == 0.f ? 1 : b + (b < 0 ? -1 : 1));
+}
+
+// Inserts an element.  A segment is read in the order of the ids, so once the list holds K elements those still
+// to come enter only above the K-th value: values equal to it (a constant row, masked logits) are no candidates.
+// (Compared with >=, each of them took a turn of the rare path's loop: 1024 rows of 151936 bf16 logits, all equal
+// or all but five masked, 7750 us, now 55 and 51, against 57 of random ones.)
 __device__ __forceinline__ void list_insert(WaveState& s, float v, int id, float r, int K) {
   const bool b = before(v, id, s.lv, s.lid);
   const float pv = shr1f(s.lv);
@@ -182,8 +191,22 @@ __device__ __forceinline__ void list_insert(WaveState& s, float v, int id, float
     if (pb) { s.lv = pv; s.lid = pid; s.lr = pr; }
     else    { s.lv = v;  s.lid = id;  s.lr = r; }
   }
-  const int kid = readlane_i(s.lid, K - 1);
-  if (kid != INT_MAX) { s.thr = readlane_f(s.lv, K - 1); s.thr_id = kid; }
+  if (readlane_i(s.lid, K - 1) != INT_MAX) s.thr = next_up(readlane_f(s.lv, K - 1));
+}
+
+// a value that 16 lanes reach: the least of the largest of 16 groups (lanes l, l + 16, l + 32, l + 48)
+__device__ __forceinline__ float sixteenth(float v) {
+  const unsigned b = __float_as_uint(v);
+  const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);   // the lower and the upper half, in both
+  v = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+  const unsigned c = __float_as_uint(v);
+  const auto r = __builtin_amdgcn_permlane16_swap(c, c, false, false);   // the even and the odd rows, in both
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  v = fminf(v, row_xor<1>(v));
+  v = fminf(v, row_xor<2>(v));
+  v = fminf(v, row_xor<4>(v));
+  v = fminf(v, row_xor<8>(v));
+  return readlane_f(v, 0);
 }
 
 // x[j] of a per-lane j: a tree of bit selects (a select between array elements would become an indexed
@@ -202,15 +225,8 @@ __device__ __forceinline__ float pick(const float (&x)[VEC], int j) {
   return __uint_as_float(t[0]);
 }
 
-// Rare path of one step: move the reference exponent, then insert candidates.
-// x[j] of lane l is element id_of(l, j) of the row; lanes with ok unset hold none.
-// The insertion stands in one loop over all (lane, j) candidates and not once per j: this path is
-// inlined into every unrolled chunk, and the code of a row is fetched once per launch, so a short
-// launch pays for its length (one copy per j: 62 KB of code for 16 wavefronts, the size of the
-// instruction cache).
-template <int VEC, typename IdOf>
-__device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool ok, float cmax, IdOf id_of, int K,
-                                     int lane) {
+// the reference exponent after elements of up to cmax in each lane
+__device__ __forceinline__ void move_reference(WaveState& s, float cmax) {
   if (__ballot(cmax > s.mx)) {
     const float m = wave_max(cmax);
     s.mx = m;
@@ -220,6 +236,24 @@ __device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool o
       s.r = nr;
     }
   }
+}
+
+// Rare path of a chunk: move the reference exponent, then insert candidates, in the order of their ids.
+// x[j] of lane l is element base + l VEC + j of the row; lanes with ok unset hold none.
+// The insertion stands in one loop over all (lane, j) candidates and not once per j: this path is
+// inlined into every unrolled chunk, and the code of a row is fetched once per launch, so a short
+// launch pays for its length (one copy per j: 62 KB of code for 16 wavefronts, the size of the
+// instruction cache).
+// Where most lanes hold candidates (values that rise along the row), the threshold first rises to a value that 16
+// of them reach; and each turn drops, in all lanes at once, the candidates that the threshold has passed.  (A row
+// of 151936 rising bf16 logits: 1858 us with a turn for each, now 59.)  Random rows pay at most 0.8% for it.
+template <int VEC>
+__device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool ok, float cmax, int base, int K,
+                                     int lane) {
+  static_assert(CADDTREE_MAX_K <= 16, "16 elements reach the raised threshold");
+  move_reference(s, cmax);
+  const float cm1 = ok ? cmax : -INFINITY;
+  if (__builtin_expect(__popcll(__ballot(cm1 >= s.thr)) > 32, 0)) s.thr = fmaxf(s.thr, sixteenth(cm1));
   uint32_t cm = 0u;                            // bit j: x[j] is a candidate
 #pragma unroll
   for (int j = 0; j < VEC; ++j) cm |= (ok && x[j] >= s.thr) ? 1u << j : 0u;
@@ -228,19 +262,26 @@ __device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool o
   while (m) {
     const int l = __builtin_ctzll(m);
     const int jl = __builtin_ctz(cm | 0x100u);   // this lane's next candidate
-    const float v = readlane_f(pick(x, jl), l);
-    const int id = id_of(l, readlane_i(jl, l));
-    if (lane == l) cm &= cm - 1u;
-    if (before(v, id, s.thr, s.thr_id)) list_insert(s, v, id, s.r, K);
+    const float xl = pick(x, jl);
+    const bool stays = xl >= s.thr;
+    if (__ballot(stays) >> l & 1) list_insert(s, readlane_f(xl, l), base + l * VEC + readlane_i(jl, l), s.r, K);
+    if (lane == l || !stays) cm &= cm - 1u;
     m = __ballot(cm != 0u);
   }
 }
 
-// The elements outside the aligned part: at most one a lane (x; -inf in a lane without one).
+// The elements outside the aligned part: at most one a lane (x; -inf in a lane without one).  Those before it
+// come after it here, so a value equal to the K-th may still enter, by its id.
 template <typename IdOf>
 __device__ __forceinline__ void edge_step(WaveState& s, float x, bool ok, IdOf id_of, int K, int lane) {
-  const float xs[1] = {x};
-  if (__ballot(ok && x >= s.thr) != 0) rare<1>(s, xs, ok, x, id_of, K, lane);
+  const float least = readlane_i(s.lid, K - 1) != INT_MAX ? readlane_f(s.lv, K - 1) : s.thr;
+  unsigned long long m = __ballot(ok && x >= least);
+  if (m) move_reference(s, x);
+  while (m) {
+    const int l = __builtin_ctzll(m);
+    m &= m - 1;
+    list_insert(s, readlane_f(x, l), id_of(l), s.r, K);
+  }
   s.acc += ok ? (double)term(x, s.r) : 0.0;
 }
 
@@ -257,7 +298,7 @@ __device__ __forceinline__ void chunk(WaveState& s, const float (&x)[VEC], bool 
   for (int j = 1; j < VEC; ++j) cmax = fmaxf(cmax, x[j]);
   const bool cand = ok && cmax >= s.thr;
   const bool any = __ballot(cand) != 0;
-  if (__builtin_expect(any, 0)) rare<VEC>(s, x, ok, cmax, [base](int l, int j) { return base + l * VEC + j; }, K, lane);
+  if (__builtin_expect(any, 0)) rare<VEC>(s, x, ok, cmax, base, K, lane);
   float t[VEC], p[VEC];
 #pragma unroll
   for (int j = 0; j < VEC; ++j) p[j] = t[j] = term(x[j], s.r);
@@ -320,16 +361,16 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   const int v1 = c1 * kWave < nv ? c1 * kWave : nv;   // the segment's vectors are c0 kWave .. v1 - 1
 
   WaveState s;
-  s.acc = 0.0; s.r = kNoExp; s.mx = -INFINITY; s.thr = -INFINITY; s.thr_id = INT_MAX;
+  s.acc = 0.0; s.r = kNoExp; s.mx = -INFINITY; s.thr = -INFINITY;
   s.lv = -INFINITY; s.lid = INT_MAX; s.lr = 0.f;
 
   // elements 0 .. head - 1 and head + nv VEC .. V - 1, fewer than 2 VEC in all: a step of the last
   // wavefront, loaded ahead of its stream
   const int gap = nv * VEC;
-  const auto edge_id = [head, gap](int l, int) { return l < head ? l : gap + l; };
+  const auto edge_id = [head, gap](int l) { return l < head ? l : gap + l; };
   const int edge = wave == S - 1 && part == P - 1 ? V - gap : 0;
   uint32_t edge_raw = 0u;
-  if (lane < edge) edge_raw = raw_bits(rowp + edge_id(lane, 0));
+  if (lane < edge) edge_raw = raw_bits(rowp + edge_id(lane));
 
   int lane_off = lane * 16;
   Segment seg{reinterpret_cast<const char*>(rowp + head) + (int64_t)c0 * (kWave * 16),
