@@ -45,6 +45,7 @@ struct WideShared {
   int res_flag;
   int cut;                     // some node of the set has a child outside it
   int la_part;                 // compaction: kept nodes of la's chunk below la
+  int reached;                 // count_tau: the depths with a node within the range
 };
 
 __host__ __device__ constexpr size_t wide_lds_bytes(size_t LK, size_t S) {
@@ -202,19 +203,23 @@ __device__ double wide_raise(const Lds& s, WideShared& x, int& la, int& lb, int 
   return t2;
 }
 
-// The threshold that about `need` nodes reach, from a count of the nodes per value of sigma: sigma is a sum of
+// The threshold that about `want` nodes reach, from a count of the nodes per value of sigma: sigma is a sum of
 // one log-probability per depth, so the nodes of depth d per value are those of depth d - 1 shifted by each
-// rank's log-probability, added up.  Counted in kCountBins bins of `range` nats in all (a rank's shift is
-// rounded to a bin, an error of a fraction of a bin that grows with the root of the depth).  Returns NaN when
-// fewer nodes than wanted lie within the range.  Called by every thread; one barrier a depth.
+// rank's log-probability, added up.  Counted in kCountBins bins of kCountRange nats in all (a rank's shift is
+// rounded to a bin, an error of a fraction of a bin that grows with the root of the depth: some 5% of the nodes at
+// depth 16, which the margin of `want` covers).  Returns NaN when fewer nodes than wanted lie within the range.
+// Called by every thread; one barrier a depth.
 //
 // A first threshold a fixed distance below the top node let a level overflow the set again and again, and every
 // in-place raise (a histogram of the set, a compaction, the level built anew) costs as much as several levels.
-// With the count a round is built once, without a raise (sets of 4400 nodes for trees of 4096, 1110 for 1024):
-// 64 rounds of 4096 nodes (L = 32, K = 16) 95.5 -> 62 us, of 1024 nodes (L = 16, K = 8) 42 -> 37.5.  One read at
-// a time and every depth counted, the count took 53 us of the first; four reads in flight and no bin below the
-// one where the count is reached, about 8.
+// With the count a round is built once, without a raise.  Expansion of 64 rounds of 4096 nodes (L = 32, K = 16),
+// flat to sharp rows (Gumbel noise with a peak over a temperature of 3, 1, 0.3 and 0.1): 56, 122, 197 and 197 us
+// without the count, 54, 73, 106 and 101 with it; of 1024 nodes (L = 16, K = 8) 51, 49, 60 and 172, now 31, 46, 50
+// and 52.  A finer count over 16 nats before it (sets 6% instead of 10% larger than the tree) made flat and sharp rows
+// pay for both: 62, 75, 106 and 122, and 35, 48, 53 and 63.
 constexpr int kCountBins = 1024;
+constexpr double kCountRange = 48.0;
+__host__ __device__ constexpr double count_want(int need) { return 1.1 * (double)need + 8.0; }
 
 // The first bin at which the running count reaches `want` (kCountBins: none), the same in every thread; t is
 // LDS for the counts, which an earlier call's readers are done with (a barrier since).
@@ -242,14 +247,14 @@ __device__ int count_reached(float* t, const float (&total)[kCountBins / (NW * k
 }
 
 template <int NW>
-__device__ double count_tau(const Lds& s, const WideShared& x, int L, int K, double range, double want, int lane,
-                            int tid) {
+__device__ double count_tau(const Lds& s, WideShared& x, int L, int K, double want, int lane, int tid) {
   constexpr int kPer = kCountBins / (NW * kW);           // bins a thread: tid, tid + NW 64, ..
   static_assert(kPer * NW * kW == kCountBins, "every bin has a thread");
   float* buf = reinterpret_cast<float*>(s.dl);           // two depths' counts (free before the set is selected)
-  const double inv_w = (double)kCountBins / range;
+  const double inv_w = (double)kCountBins / kCountRange;
+  const int w = __builtin_amdgcn_readfirstlane(tid / kW);
   float total[kPer];
-  __syncthreads();                                       // an earlier count's readers are done
+  if (tid == 0) x.reached = 0;
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
     total[u] = 0.f;
@@ -258,10 +263,18 @@ __device__ double count_tau(const Lds& s, const WideShared& x, int L, int K, dou
   __syncthreads();
   int cur = 0;
   int lim = kCountBins - 1;                              // the threshold lies in this bin or above
+  const int lk = lane < K ? lane : 0;
+  double Ad = x.A[0], An = x.A[1];
+  float tl = s.tl[lk];
   for (int d = 0; d < L; ++d) {
-    const double lq = lane < K ? (double)s.tl[d * K + (lane < K ? lane : 0)] - (x.A[d + 1] - x.A[d]) : -INFINITY;
+    const double lq = lane < K ? (double)tl - (An - Ad) : -INFINITY;
+    const int dn = d + 1 < L ? d + 1 : d;                // the next depth's, ahead of this one's sums
+    Ad = x.A[dn];
+    An = x.A[dn + 1];
+    tl = s.tl[dn * K + lk];
     const int q = (int)fmax(fmin(0.5 - lq * inv_w, (double)kCountBins), 0.0);   // (NaN: out of range)
-    const int nr = __popcll(__ballot(q < kCountBins));   // ranks within the range (they fall with the rank)
+    // ranks within the range (they fall with the rank); none where the wavefront's bins lie below the threshold's
+    const int nr = w * kW <= lim ? __popcll(__ballot(q < kCountBins)) : 0;
     const float* from = buf + cur * kCountBins;
     float h[kPer];
 #pragma unroll
@@ -293,9 +306,12 @@ __device__ double count_tau(const Lds& s, const WideShared& x, int L, int K, dou
       total[u] += h[u];
       some = some || h[u] > 0.f;
     }
-    if (__syncthreads_or(some ? 1 : 0) == 0) break;      // no deeper node lies within the range
+    if (some) x.reached = d + 1;
+    __syncthreads();
+    if (x.reached <= d) break;                           // no deeper node lies within the range
     // once the count is reached, what lies below that bin no longer matters: the count's depth is then the
-    // tree's and not that of the whole range
+    // tree's and not that of the whole range.  A look costs a barrier and a scan, so there are three: trees of 4096
+    // nodes have that many down to depth 3 with 16 ranks, 5 with 5 and 8 with 3, if all lie within the range.
     if (d == 2 || d == 4 || d == 7) {
       const int at = count_reached<NW>(reinterpret_cast<float*>(s.sl), total, want, lane, tid);
       lim = at < lim ? at : lim;
@@ -428,7 +444,7 @@ expand_wide_kernel(const int32_t* __restrict__ topk_ids, const float* __restrict
                    const double* __restrict__ lse, int L, int K, int cap, CostTables ct, int fixed, int setcap,
                    int32_t* __restrict__ token_ids, int32_t* __restrict__ parent_out,
                    int32_t* __restrict__ depth_out, float* __restrict__ path_prob, int32_t* __restrict__ n_star_out,
-                   float* __restrict__ phi_out, float* __restrict__ theta_out) {
+                   float* __restrict__ phi_out, float* __restrict__ theta_out, int countable) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
@@ -461,10 +477,9 @@ expand_wide_kernel(const int32_t* __restrict__ topk_ids, const float* __restrict
   const double top = pmin(0.0 + (double)s.tl[0] - A1, 0.0);   // the first node to pop
   int need = cap;                            // the tree keeps cap nodes before any stop test
   bool tight = true;
-  // the counted threshold, with a margin for the bins' rounding; a fixed distance below the top node where
-  // the count's ranges hold too few nodes
-  double tau = count_tau<NW>(s, x, L, K, 16.0, 1.06 * (double)need + 8.0, lane, tid);
-  if (!(tau < 0.0)) tau = count_tau<NW>(s, x, L, K, 48.0, 1.12 * (double)need + 8.0, lane, tid);
+  // the counted threshold; a fixed distance below the top node where the range, or the whole tree, holds too
+  // few nodes
+  double tau = countable ? count_tau<NW>(s, x, L, K, count_want(need), lane, tid) : NAN;
   bool counted = tau < 0.0;
   if (!counted) tau = top - drop_fixed(need);
   tau = fmin(tau, top);
@@ -666,6 +681,14 @@ expand_wide_kernel(const int32_t* __restrict__ topk_ids, const float* __restrict
 
 }  // namespace
 
+// Whether the whole tree of L depths of K ranks holds the nodes that a round of `cap` counts (else the count is
+// known to fail: K = 2, L = 8 under a cap of 512 took 17 us more for nothing).
+bool expand_wide_countable(int32_t L, int32_t K, int32_t cap) {
+  double nodes = 0.0;
+  for (int d = 0; d < L; ++d) nodes = (nodes + 1.0) * (double)K;
+  return nodes >= count_want(cap);
+}
+
 bool expand_wide_applies(int32_t cap, bool lean) { return lean && cap >= kWideMinNodes; }
 
 size_t expand_wide_lds_bytes(int32_t L, int32_t K, int32_t set_cap) {
@@ -687,15 +710,16 @@ hipError_t expand_wide_prepare() {
 hipError_t launch_expand_wide(const ExpandArgs& a, hipStream_t stream) {
   if (a.B == 0) return hipSuccess;
   const size_t lds = expand_wide_lds_bytes(a.L, a.K, a.level_set_cap);
+  const int countable = expand_wide_countable(a.L, a.K, a.cap) ? 1 : 0;
   const bool sixteen = a.B <= (int64_t)a.num_cu || 2 * lds > (size_t)160 * 1024;
   if (sixteen)
     hipLaunchKernelGGL(expand_wide_kernel<16>, dim3((unsigned)a.B), dim3(16 * kW), lds, stream, a.topk_ids,
                        a.topk_logit, a.lse, a.L, a.K, a.cap, a.cost, a.fixed_budget ? 1 : 0, a.level_set_cap,
-                       a.token_ids, a.parent, a.depth, a.path_prob, a.n_star, a.phi, a.theta);
+                       a.token_ids, a.parent, a.depth, a.path_prob, a.n_star, a.phi, a.theta, countable);
   else
     hipLaunchKernelGGL(expand_wide_kernel<8>, dim3((unsigned)a.B), dim3(8 * kW), lds, stream, a.topk_ids,
                        a.topk_logit, a.lse, a.L, a.K, a.cap, a.cost, a.fixed_budget ? 1 : 0, a.level_set_cap,
-                       a.token_ids, a.parent, a.depth, a.path_prob, a.n_star, a.phi, a.theta);
+                       a.token_ids, a.parent, a.depth, a.path_prob, a.n_star, a.phi, a.theta, countable);
   return hipGetLastError();
 }
 

@@ -98,6 +98,7 @@ hipError_t expand_level_prepare();        // raises the batched kernel's dynamic
 // The several-wavefront batched kernel (expand_wide.hip): trees that keep a known number of nodes
 // (a fixed budget, or a cost flat up to the cap) of at least 512.
 bool expand_wide_applies(int32_t cap, bool lean);
+bool expand_wide_countable(int32_t L, int32_t K, int32_t cap);   // its first threshold may be counted
 size_t expand_wide_lds_bytes(int32_t L, int32_t K, int32_t set_cap);
 hipError_t expand_wide_prepare();
 // Rounds it cannot settle are flagged (n_star = -1) for the serial kernel.

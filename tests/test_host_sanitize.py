@@ -163,6 +163,15 @@ int main() {
             EXPECT(caddtree_workspace_bytes(&p, B) >= table(p, B) &&
                    caddtree_workspace_bytes(&p, B) <= std::max(most, table(p, B)));
         }
+  // the several-wavefront expansion counts nodes for its first threshold only where the tree can hold the count
+  for (int K = 1; K <= 16; ++K)
+    for (int L = 1; L <= 32; ++L)
+      for (int cap : {512, 513, 700, 1024, 4096}) {
+        double nodes = 0.0, width = 1.0;
+        for (int d = 0; d < L; ++d) nodes += width *= K;
+        EXPECT(nodes >= cap || !caddtree::expand_wide_countable(L, K, cap));
+        EXPECT(nodes < 1.2 * cap || caddtree::expand_wide_countable(L, K, cap));
+      }
   std::printf("sizes done, %d failures\n", fails);
   return fails == 0 ? 0 : 1;
 }
