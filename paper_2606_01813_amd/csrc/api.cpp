@@ -106,7 +106,7 @@ size_t topk_workspace(const caddtree_plan* p, int64_t B, const caddtree_outputs_
 
 // The launch shape of a reduction of `rows` rows; may_split: there is memory for partial results.
 caddtree::ReduceShape reduce_shape(const caddtree_plan* p, int64_t rows, bool may_split) {
-  return caddtree::reduce_default_shape(rows, (int32_t)p->V, p->K, p->dtype, may_split);
+  return caddtree::reduce_default_shape(rows, (int32_t)p->V, p->K, p->dtype, may_split, p->num_cu);
 }
 
 // The parts of a row in a build of B rounds with `bytes` of workspace past the top-K table's (1: not split),

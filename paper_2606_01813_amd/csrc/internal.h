@@ -34,7 +34,8 @@ struct ReduceShape {
   int32_t unroll;  // 16-byte loads in flight per lane
   int32_t split;   // parts per row
 };
-ReduceShape reduce_default_shape(int64_t rows, int32_t V, int32_t K, caddtree_dtype_t dtype, bool may_split);
+ReduceShape reduce_default_shape(int64_t rows, int32_t V, int32_t K, caddtree_dtype_t dtype, bool may_split,
+                                 int32_t num_cu);
 // a row's partial results: per part a sum (fp64) and its exponent, and K keys (64 bits) and values
 constexpr int32_t split_row_bytes(int32_t K, int32_t split) { return (split * (12 + 12 * K) + 15) / 16 * 16; }
 

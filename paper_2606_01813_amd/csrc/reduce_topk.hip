@@ -571,29 +571,36 @@ hipError_t launch_t(const ReduceArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-// Launch shape, from sweeps of the shapes over 16 .. 22400 rows of 3000 .. 151936 logits (times in us).
-// - Large batches: one wave per row, 8 loads in flight (8192 rows of 151936 fp32: 728, with 4 loads 735), but 4
+// Launch shape, from sweeps of the shapes over 16 .. 22400 rows of 3000 .. 151936 logits (times in us).  `full` is
+// the waves of a full chip at four per SIMD, 4096 on 256 compute units.
+// - More rows than that: one wave per row, 8 loads in flight (8192 rows of 151936 fp32: 728, with 4 loads 735), but 4
 //   from 4097 to 8191 rows, which then all fit on the chip (6400 rows of 151936 fp32: 582 against 595).
-// - Up to 4096 rows: the most waves per row, up to 8, that keep 4096 waves on the chip at once and leave a wave 3
+// - Else the most waves per row, up to 8, that keep `full` waves on the chip at once and leave a wave 3
 //   chunks (64 rows of 16 chunks: 1 wave 19.0, 2 waves 15.5, 4 waves 14.7; 128 rows of 63: 32.1, 25.5, 20.0, and
 //   8 waves 17.6).  16 waves are no better at any size (16 rows of 297 chunks 17.1, with 8 waves 16.6; 512
-//   rows 37.1 and 28.7).  fp32 rows of 4 waves and more on a full chip take 4 loads (1024 rows of 32000: 23.0
-//   against 24.5).
+//   rows 37.1 and 28.7).
+// - fp32 rows of 4 waves that leave no room for 8 (513 to 1024 rows) take 4 loads (against 8: 600 rows of 32000 18.7 and
+//   20.3, 800 23.5 and 25.0, 1000 25.7 and 27.5, 1024 25.7 and 27.6; of 8000 9.8 and 9.9, 11.0 and 11.1, 11.2 and 11.6,
+//   11.3 and 11.7; of 151936 59.2 and 61.6, 81.9 and 83.3, 90.8 and 92.5, 92.9 and 94.0).  With 8 waves neither is
+//   better throughout (400 rows of 32000 14.4 and 13.9, of 8000 9.0 and 9.1), with fewer waves and in bf16 8 loads are as
+//   good or better (1025 fp32 rows of 8000 12.7 and 12.0; 600 bf16 rows of 32000 18.0 and 16.5).
 // - So few rows that compute units are left idle, where there is memory for partial results: up to 4 parts per
 //   row, at most a compute unit's worth of parts each, and 4 chunks a wave (a build of 16 rows of 297 chunks:
 //   25.6, in two parts 23.1, in four 20.9, in eight 22.9, since the merge grows with the parts; 128 rows: 28.1,
 //   24.6, 26.1; 192 rows: 27.8, 30.2; 8 rows of 125 chunks: 16.0, 15.9, 15.7).
-ReduceShape reduce_default_shape(int64_t rows, int32_t V, int32_t K, caddtree_dtype_t dtype, bool may_split) {
+ReduceShape reduce_default_shape(int64_t rows, int32_t V, int32_t K, caddtree_dtype_t dtype, bool may_split,
+                                 int32_t num_cu) {
   const int CH = kWave * (dtype == CADDTREE_BF16 ? 8 : 4);
   const int nch = (V + CH - 1) / CH;
+  const int64_t full = 16 * (int64_t)num_cu;
   ReduceShape sh{1, 8, 1};
-  if (rows > 4096) {
-    sh.unroll = rows >= 8192 ? 8 : 4;
+  if (rows > full) {
+    sh.unroll = rows >= 2 * full ? 8 : 4;
     return sh;
   }
-  while (sh.waves < 8 && rows * sh.waves * 2 <= 4096 && nch / (2 * sh.waves) >= 3) sh.waves *= 2;
-  if (dtype == CADDTREE_F32 && sh.waves >= 4 && rows >= 1024) sh.unroll = 4;
-  while (may_split && sh.split < 4 && rows * sh.split * 2 <= 256 && 2 * sh.split * K <= kWave &&
+  while (sh.waves < 8 && rows * sh.waves * 2 <= full && nch / (2 * sh.waves) >= 3) sh.waves *= 2;
+  if (dtype == CADDTREE_F32 && sh.waves == 4 && rows * 8 > full) sh.unroll = 4;
+  while (may_split && sh.split < 4 && rows * sh.split * 2 <= num_cu && 2 * sh.split * K <= kWave &&
          nch / (2 * sh.split * sh.waves) >= 4)
     sh.split *= 2;
   return sh;

@@ -163,6 +163,20 @@ int main() {
             EXPECT(caddtree_workspace_bytes(&p, B) >= table(p, B) &&
                    caddtree_workspace_bytes(&p, B) <= std::max(most, table(p, B)));
         }
+  // a launch shape holds over a range of rows, from one number to at least half as many again
+  for (int64_t V : {300, 4096, 8000, 32000, 64000, 100003, 151936})
+    for (int dt : {CADDTREE_F32, CADDTREE_BF16})
+      for (bool parts : {false, true}) {
+        caddtree_plan p = {};
+        p.L = 1; p.K = 8; p.V = V; p.dtype = (caddtree_dtype_t)dt; p.num_cu = 256;
+        int64_t from = 1;
+        for (int64_t rows = 2; rows <= 9000; ++rows) {
+          const caddtree::ReduceShape a = reduce_shape(&p, rows - 1, parts), b = reduce_shape(&p, rows, parts);
+          if (a.waves == b.waves && a.unroll == b.unroll && a.split == b.split) continue;
+          EXPECT(2 * (rows - 1) >= 3 * from);
+          from = rows;
+        }
+      }
   // the several-wavefront expansion counts nodes for its first threshold only where the tree can hold the count
   for (int K = 1; K <= 16; ++K)
     for (int L = 1; L <= 32; ++L)
