@@ -2,10 +2,9 @@
 // top-K list, and the partial results of a row that several workgroups reduce.
 //
 // A launch of few rows leaves most of the chip idle when a row belongs to one workgroup.  Such a row is cut
-// into P parts, one workgroup each, that leave a partial result in the workspace: the K best of the part with
-// the reference exponents at their insertion, the sum of the terms and its reference exponent.  The expansion
-// kernel's prologue merges them (one wavefront a row, the part's K best one candidate a lane, P K <= 64), so
-// the split costs no launch of its own.
+// into P parts, one workgroup each, that leave a partial result in the workspace: the K best of the part, the sum
+// of the terms and its reference exponent.  The expansion kernel's prologue merges them (one wavefront a row, the
+// parts' K best one candidate a lane, P K <= 64), so the split costs no launch of its own.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -45,7 +44,7 @@ __device__ __forceinline__ int key_id(uint64_t k) { return INT_MAX - (int)(uint3
 // One row's partial results, P parts (split_row_bytes(K, P) bytes a row)
 struct PartRow {
   uint64_t* key;  // [P, K] the K best of each part, as keys
-  double* sum;    // [P] sum of the part's terms, relative to r, its K best in fp64
+  double* sum;    // [P] sum of the part's terms, relative to r
   float* r;       // [P]
   float* v;       // [P, K] the values as read (the sign of a zero included)
 };
@@ -59,17 +58,6 @@ __device__ __forceinline__ PartRow part_row(void* parts, int64_t row, int K, int
   return p;
 }
 
-// The sum relative to R with the fp32 terms of the list (lane k < K: the k-th best), recomputed bit for bit,
-// replaced by fp64 values.  Called by a whole wavefront.
-__device__ __forceinline__ double corrected_sum(double sum, float R, float lv, float lr, int K, int lane) {
-  double corr = 0.0;
-  if (lane < K) {
-    const double approx = ldexp((double)term(lv, lr), (int)fmaxf(lr - R, -2000.f));
-    const double exact = exp2((double)lv * kLog2eD - (double)R);
-    corr = exact - approx;
-  }
-  return sum + xp::rl_d(xp::wave_incl_scan(corr), 63);
-}
 __device__ __forceinline__ double lse_of(double sum, float R) { return (double)R * kLn2D + log(sum); }
 
 // A row's partial results as a wavefront holds them: lane i < P K one candidate, lane p < P a part's sum.

@@ -1179,7 +1179,7 @@ def _rows_of(kind, shape, rng):
 def test_k1_equal_masked_and_rising_rows(kind, dtype, waves, monkeypatch):
     """Values equal to the K-th are no candidates once a list is full, except among the few elements before a
     row's aligned part, which are read last.  The normaliser's error is at most that of a term: its argument, in
-    (2, 3] for the largest, is rounded twice to 2^-23, and its exp2 to 2^-23."""
+    (3, 4] for the largest, is rounded twice to 2^-23, and its exp2 to 2^-23."""
     import torch
     monkeypatch.setenv("CADDTREE_K1_WAVES", str(waves))
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
@@ -1230,3 +1230,36 @@ def test_k1_equal_and_masked_rows_take_no_longer(kind):
             times.append(a.elapsed_time(b))
         took[k] = sorted(times)[4]
     assert took[kind] <= 6.0 * took["random"], took
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,K,temp,rows,limit", [
+    (151936, 2, 0.3, 64, 4.0e-9),      # sharp: 2.1e-9; with the row's K best alone in fp64 6e-9
+    (151936, 8, 0.3, 64, 3.0e-10),     # 5e-11, 7e-10
+    (100, 4, 3.0, 1024, 7.0e-9),       # one ragged chunk: 5.4e-9; its terms added in pairs in fp32 8 to 9.6e-9
+    (5001, 8, 1.0, 512, 1.6e-8),       # rows off a 16-byte boundary: 1.2e-8; every term added in fp64, the reference at
+    (100003, 10, 1.0, 240, 1.8e-8),    # the maximum, 2.3e-8 and 2.2e-8 (here 1.3e-8)
+    (151936, 8, 1.0, 256, 1.9e-8),     # aligned, 1.4e-8; likewise 2.2e-8
+])
+def test_k1_normaliser_error(dtype, V, K, temp, rows, limit):
+    """The rms error of the normaliser against 64 bits, Gumbel noise with a peak over a temperature.  Each limit
+    lies between what the kernel has and what it had where the terms were kept otherwise."""
+    import torch
+    L = 16
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cfg = synth.get_config("c1").replace(V=V, B=4, L=L, K=K, cap=8, dtype=dtype)
+    plan = make_plan(cfg)
+    total, n = 0.0, 0
+    for seed in range(max(rows // 64, 1)):
+        g = torch.Generator(device="cuda").manual_seed(100 + seed)
+        u = torch.rand((cfg.B, L, V), generator=g, device="cuda", dtype=torch.float64).clamp_(min=2.0 ** -53)
+        x = -(-u.log()).log()
+        peak = torch.randint(0, V, (cfg.B, L, 1), generator=g, device="cuda")
+        x.scatter_add_(2, peak, 2 + 8 * torch.rand((cfg.B, L, 1), generator=g, device="cuda", dtype=torch.float64))
+        x = (x / temp).to(tdt)
+        out = plan.new_outputs(cfg.B, topk=True)
+        plan.reduce_topk(x, out.topk_ids, out.topk_logit, out.lse)
+        d = out.lse - torch.logsumexp(x.double(), dim=2)
+        total += float((d * d).sum())
+        n += d.numel()
+    assert (total / n) ** 0.5 <= limit, (total / n) ** 0.5
