@@ -371,7 +371,7 @@ caddtree_status_t caddtree_plan_create(const caddtree_config_t* cfg, caddtree_pl
   p->k1_waves = 0;
   if (const char* env = std::getenv("CADDTREE_K1_WAVES")) {
     const int w = std::atoi(env);
-    if (w == 1 || w == 2 || w == 4 || w == 8 || w == 16) p->k1_waves = w;
+    if (w == 1 || w == 2 || w == 4 || w == 8) p->k1_waves = w;
   }
   p->k1_split = 0;
   if (const char* env = std::getenv("CADDTREE_K1_SPLIT")) {

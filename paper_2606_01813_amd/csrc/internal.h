@@ -19,7 +19,7 @@ struct ReduceArgs {
   int64_t row_stride;    // elements
   int32_t V;
   int32_t K;
-  int32_t waves_per_row; // 1 .. 16
+  int32_t waves_per_row; // 1, 2, 4 or 8
   int32_t unroll;        // 16-byte loads in flight per lane: 4 or 8
   int32_t split;         // parts a row is cut into, a workgroup each; above 1 the results go to `parts`
   void* parts;           // [rows, split_row_bytes(K, split)] when split > 1

@@ -41,6 +41,7 @@ namespace {
 using namespace red;
 
 constexpr int kWave = 64;
+constexpr int kMaxWaves = 8;                    // wavefronts per row
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Streaming 16-byte loads of a wavefront's segment, with the non-temporal hint (each byte of the logits is
@@ -243,8 +244,8 @@ __device__ __forceinline__ void move_reference(WaveState& s, float cmax) {
 // x[j] of lane l is element base + l VEC + j of the row; lanes with ok unset hold none.
 // The insertion stands in one loop over all (lane, j) candidates and not once per j: this path is
 // inlined into every unrolled chunk, and the code of a row is fetched once per launch, so a short
-// launch pays for its length (one copy per j: 62 KB of code for 16 wavefronts, the size of the
-// instruction cache).
+// launch pays for its length (one copy per j: 62 KB of code, the size of the instruction
+// cache).
 // Where most lanes hold candidates (values that rise along the row), the threshold first rises to a value that 16
 // of them reach; and each turn drops, in all lanes at once, the candidates that the threshold has passed.  (A row
 // of 151936 rising bf16 logits: 1858 us with a turn for each, now 59.)  Random rows pay at most 0.8% for it.
@@ -332,9 +333,9 @@ __device__ __forceinline__ void unpack(const uint4& q, float (&x)[4]) {
 __device__ __forceinline__ uint32_t raw_bits(const float* p) { return __float_as_uint(*p); }
 __device__ __forceinline__ uint32_t raw_bits(const uint16_t* p) { return *p; }
 
-// kUnroll: 16-byte loads in flight per lane (4 or 8); kS: wavefronts per row (1 .. 16)
+// kUnroll: 16-byte loads in flight per lane (4 or 8); kS: wavefronts per row (1, 2, 4 or 8)
 template <typename T, int kUnroll, int kS>
-__global__ void __launch_bounds__(1024)
+__global__ void __launch_bounds__(kWave * kMaxWaves)
 reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int K,
                    int32_t* __restrict__ out_ids, float* __restrict__ out_logit,
                    float* __restrict__ out_lq, double* __restrict__ out_lse, void* __restrict__ parts) {
@@ -566,7 +567,6 @@ hipError_t launch_u(const ReduceArgs& a, hipStream_t stream) {
     case 2: launch_s<T, U, 2>(a, stream); break;
     case 4: launch_s<T, U, 4>(a, stream); break;
     case 8: launch_s<T, U, 8>(a, stream); break;
-    case 16: launch_s<T, U, 16>(a, stream); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
