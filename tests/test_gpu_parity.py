@@ -1263,3 +1263,77 @@ def test_k1_normaliser_error(dtype, V, K, temp, rows, limit):
         total += float((d * d).sum())
         n += d.numel()
     assert (total / n) ** 0.5 <= limit, (total / n) ** 0.5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("waves,unroll", [(1, 8), (4, 4), (8, 8)])
+@pytest.mark.parametrize("split", [2, 4, 8])
+def test_split_masked_and_tied_rows(split, waves, unroll, dtype, monkeypatch):
+    """Parts without a finite logit, values equal across the parts' bounds and zeros of both signs at the K-th
+    place, merged by the prologue and by the merge kernel: the top-K table and the normaliser against 64 bits."""
+    import torch
+    for k, v in (("SPLIT", split), ("WAVES", waves), ("UNROLL", unroll)):
+        monkeypatch.setenv("CADDTREE_K1_" + k, str(v))
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rng = np.random.default_rng(13)
+    bound = (2 * np.log(2.0) + 1) * 2.0 ** -23
+    K = 8
+    for V in (40, 20011):
+        kinds = ["random", "constant", "tied", "masked", "lowest", "prefix", "rising", "zeros"]
+        x = np.stack([_rows_of(k, (4, V), rng) for k in kinds])
+        zero = rng.random((4, V)) < 0.5
+        x[-1] = np.where(zero, 0.0, -0.0) - (rng.random((4, V)) < 0.2)            # 0, -0 and -1
+        x[-1, :, V // 2] = 3.0
+        B, L = x.shape[:2]
+        logits = torch.from_numpy(x).to(tdt).cuda()
+        xd = logits.cpu().to(torch.float64).numpy()
+        order = np.argsort(-xd, axis=-1, kind="stable")[..., :K]
+        m = xd.max(-1)
+        lse = m + np.log(np.exp(xd - m[..., None]).sum(-1))
+        for kw in (dict(cap=40), dict(cap=600, fixed=True)):
+            cfg = synth.get_config("c1").replace(V=V, B=B, L=L, K=K, dtype=dtype, **kw)
+            plan = make_plan(cfg)
+            out = plan.new_outputs(B, topk=True)
+            plan.build(logits, out, workspace=plan.new_workspace(B))
+            torch.cuda.synchronize()
+            h = host(out)
+            assert np.array_equal(h["topk_ids"], order), V
+            top = np.take_along_axis(xd, order, -1)
+            assert np.array_equal(h["topk_logit"].astype(np.float64), top), V
+            assert np.array_equal(np.signbit(h["topk_logit"]), np.signbit(top)), V
+            assert np.abs(h["lse"] - lse).max() <= bound, V
+            lq = top - h["lse"][..., None]
+            np.testing.assert_allclose(h["topk_lq"], lq, rtol=2.0 ** -23)
+
+
+@pytest.mark.parametrize("B,cap,in_place", [(3, 300, True), (300, 4096, False)])
+def test_split_rows_left_to_the_serial_form(B, cap, in_place, monkeypatch):
+    """The merging kernel's rounds that it cannot settle: constant logits of 16 ranks, and a cost flat up to 300
+    nodes.  A threshold set holds 272 nodes (two depths) or 4368 (three), and the stop needs more than 300 while the
+    set takes 1024, so every round goes to the serial form, in the same workgroup (its layout is small, or every
+    round has a compute unit) or in the kernel after it, which reads the table that the merge wrote."""
+    import oracle
+    import torch
+    from paper_2606_01813_amd import Plan
+    L, V, K = 4, 1000, 16
+    monkeypatch.setenv("CADDTREE_K1_SPLIT", "4")
+    tv = np.array([1.0 if n <= 300 else 1.0 + 0.01 * (n - 300) for n in range(cap + 1)])
+    plan = Plan(L=L, V=V, K=K, cap=cap, t_draft=1.0, t_verify=tv, dtype="f32", mask="bits", fixed_budget=in_place)
+    x = np.zeros((B, L, V), dtype=np.float32)
+    x[1] += 2.5
+    x[2] -= 7.0
+    out = plan.new_outputs(B, topk=True)
+    plan.build(torch.from_numpy(x).cuda(), out, workspace=plan.new_workspace(B))
+    torch.cuda.synchronize()
+    h = host(out)
+    rs = [oracle.build_round(x[b], "f32", K, 1.0, tv, cap, mask="bits", budget=cap if in_place else None)
+          for b in range(3)]
+    assert all(r.n_star >= 300 for r in rs)
+    first = {k: v[:3] for k, v in h.items() if v is not None}
+    compare_topk(first, rs)
+    compare_tree(first, rs, "bits", cap)
+    n = rs[0].n_star
+    for b in range(3, B):                                 # the same round as the first
+        assert h["n_star"][b] == n
+        for k in ("token_ids", "parent", "depth", "path_prob"):
+            assert np.array_equal(h[k][b, :n], h[k][0, :n]), (b, k)
