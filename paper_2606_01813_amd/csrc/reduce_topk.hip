@@ -582,7 +582,9 @@ hipError_t launch_t(const ReduceArgs& a, hipStream_t stream) {
 // Launch shape, from sweeps of the shapes over 16 .. 22400 rows of 3000 .. 151936 logits (times in us).  `full` is
 // the waves of a full chip at four per SIMD, 4096 on 256 compute units.
 // - More rows than that: one wave per row, 8 loads in flight (8192 rows of 151936 fp32: 728, with 4 loads 735), but 4
-//   from 4097 to 8191 rows, which then all fit on the chip (6400 rows of 151936 fp32: 582 against 595).
+//   for rows of at most 4 chunks (4 against 8 loads, 6400 bf16 rows of 2048: 16.9 and 17.6; of 2500, 5 chunks, 19.5 and
+//   19.0, of 4096 25.4 and 21.9, of 32000 76.8 and 73.9) and from 4097 to 8191 fp32 rows (6400 of 4000: 24.3 and 24.9, of
+//   32000 125 and 129, of 151936 582 and 595).
 // - Else the most waves per row, up to 8, that keep `full` waves on the chip at once and leave a wave 3
 //   chunks (64 rows of 16 chunks: 1 wave 19.0, 2 waves 15.5, 4 waves 14.7; 128 rows of 63: 32.1, 25.5, 20.0, and
 //   8 waves 17.6).  16 waves are no better at any size (16 rows of 297 chunks 17.1, with 8 waves 16.6; 512
@@ -603,7 +605,7 @@ ReduceShape reduce_default_shape(int64_t rows, int32_t V, int32_t K, caddtree_dt
   const int64_t full = 16 * (int64_t)num_cu;
   ReduceShape sh{1, 8, 1};
   if (rows > full) {
-    sh.unroll = rows >= 2 * full ? 8 : 4;
+    if (nch <= 4 || (dtype == CADDTREE_F32 && rows < 2 * full)) sh.unroll = 4;
     return sh;
   }
   while (sh.waves < 8 && rows * sh.waves * 2 <= full && nch / (2 * sh.waves) >= 3) sh.waves *= 2;
