@@ -63,7 +63,7 @@ typedef enum {
   CADDTREE_E_INVALID = 1,      /* bad argument: NULL where required, negative or inconsistent size */
   CADDTREE_E_UNSUPPORTED = 2,  /* valid request beyond the library's limits (L, K, cap, V) */
   CADDTREE_E_COST = 3,         /* cost model rejected: C_d <= 0, non-finite, C_v decreasing or not convex */
-  CADDTREE_E_WORKSPACE = 4,    /* workspace NULL, misaligned or smaller than caddtree_workspace_bytes() */
+  CADDTREE_E_WORKSPACE = 4,    /* workspace NULL, misaligned or too small for the top-K table */
   CADDTREE_E_HIP = 5           /* a HIP runtime call or kernel launch failed */
 } caddtree_status_t;
 
@@ -174,7 +174,8 @@ typedef struct {
  * Cor. 2), and the tree-attention mask and position ids (Sec. 3.3).
  * logits: DEVICE [B, L, row_stride] of the plan's dtype; B >= 0 (0 is a no-op).
  * workspace: DEVICE, caddtree_workspace_bytes(plan, B) bytes, 256-byte aligned
- * (may be NULL when every top-K output pointer is given).
+ * (may be NULL when every top-K output pointer is given; one that is given is
+ * then still used for the partial results of a few rounds).
  * The call only enqueues kernels on `stream` (no allocation, memset or
  * synchronisation), so it may be captured in a HIP graph; a replay reads and
  * writes the buffers given at capture. */
@@ -187,9 +188,10 @@ caddtree_status_t caddtree_build(caddtree_plan_t plan, const void* logits, int64
  * workspace argument.  The top-K table the caller does not ask for lives in a
  * device array inside the library, CADDTREE_NOALLOC_SCRATCH_BYTES per GPU, held
  * until the process ends; the call allocates and frees nothing and runs the same
- * kernels as caddtree_build, with the same results.
- *   Limit: caddtree_workspace_bytes(plan, B) for the top-K outputs left NULL
- *   must not exceed CADDTREE_NOALLOC_SCRATCH_BYTES (8 MiB: about
+ * kernels as caddtree_build with a workspace, with the same results (as without
+ * one when every top-K output is given: the array is then not used).
+ *   Limit: the table of the top-K outputs left NULL must not exceed
+ *   CADDTREE_NOALLOC_SCRATCH_BYTES (8 MiB: about
  *   2^20 / (L K + L) rounds, 7281 at L = 16, K = 8), else CADDTREE_E_WORKSPACE
  *   and nothing is enqueued.  Passing every top-K output lifts the limit.
  *   Every call on one GPU shares that GPU's array, whatever the plan or stream:
@@ -204,7 +206,9 @@ caddtree_status_t caddtree_build_noalloc(caddtree_plan_t plan, const void* logit
                                          hipStream_t stream);
 
 /* Stage 1 (Sec. 3.2): per (round, position) row, LSE in fp64 and the top-K by
- * (value desc, id asc).  topk_ids, topk_logit, lse required; topk_lq optional. */
+ * (value desc, id asc).  topk_ids, topk_logit, lse required; topk_lq optional.
+ * A row is one workgroup's here at any batch, so the last bits of lse may differ
+ * from those of a caddtree_build of a few rounds. */
 caddtree_status_t caddtree_reduce_topk(caddtree_plan_t plan, const void* logits, int64_t B, int64_t row_stride,
                                        int32_t* topk_ids, float* topk_logit, float* topk_lq, double* lse,
                                        hipStream_t stream);

@@ -515,7 +515,8 @@ caddtree_status_t run_build(const caddtree_plan* p, const void* logits, int64_t 
   // what is left of the workspace holds a split reduction's parts; without a workspace, or with one of the
   // table's size alone, a row is one workgroup's
   size_t need = 0;
-  const bool room = workspace != nullptr && workspace_bytes >= table && reinterpret_cast<uintptr_t>(workspace) % 256 == 0;
+  const bool room =
+      workspace != nullptr && workspace_bytes >= table && reinterpret_cast<uintptr_t>(workspace) % 256 == 0;
   const int32_t split = room ? build_split(p, B, workspace_bytes - table, &need) : 1;
   void* parts = split > 1 ? static_cast<char*>(workspace) + table : nullptr;
   const caddtree::MergeIn merge{parts, split, tb.ids, tb.logit, out->topk_lq, tb.lse};

@@ -7,9 +7,10 @@
 // share each pass over a level or over the set.
 //
 // The steps are those of the one-wavefront kernel (expand_level.hip), from a
-// first threshold found by counting nodes (count_tau): build T(tau) level by level, raise tau in place when a level overflows the set,
-// lower it when the set is too small, find the stop by a histogram of sigma,
-// then lay the kept nodes out in breadth-first order.  Each pass is split into
+// first threshold found by counting nodes (count_tau): build T(tau) level by
+// level, raise tau in place when a level overflows the set, lower it when the
+// set is too small, find the stop by a histogram of sigma, then lay the kept
+// nodes out in breadth-first order.  Each pass is split into
 // 64-node chunks, chunk k going to wavefront k mod NW; the steps that need the
 // whole set or level (slot offsets of a level's children, histogram totals,
 // new indices after a compaction, breadth-first positions) meet at workgroup

@@ -7,26 +7,31 @@
 // before and after it (rows of a vocabulary or a stride that is no multiple of 16
 // bytes start anywhere) are one more step of the last wavefront, one element a lane.
 // (Element loads for every row off a 16-byte boundary took 181 us for 48 x 15 rows of
-// 100003 bf16 logits; the vectors and the edge step 40, and 33 since the row-wide threshold.)
-// A wavefront streams 16-byte loads (8 bf16 or 4 fp32 per lane, 1 KiB per wave per load) and
-// keeps, per lane, an fp64 sum of 2^(x log2 e - r) where r is a wave-uniform
-// integer exponent, a little below the running maximum's, that only grows: when it moves, the sums are rescaled by an
-// exact power of two.  The exponent argument is formed with a two-part log2 e
-// (two fmas), so the only per-term error is the hardware exp2.
+// 100003 bf16 logits; the vectors and the edge step 40, and 33 with the row-wide
+// threshold.)
+// A wavefront streams 16-byte loads (8 bf16 or 4 fp32 per lane, 1 KiB per wave per
+// load) and keeps, per lane, an fp64 sum of 2^(x log2 e - r) where r is a wave-uniform
+// integer exponent, a little below the running maximum's, that only grows: when it
+// moves, the sums are rescaled by an exact power of two.  The exponent argument is
+// formed with a two-part log2 e (two fmas), so the only per-term errors are the
+// argument's rounding and the hardware exp2.
 //
 // Top-K: the wave keeps a sorted list of 16 slots in lanes 0..15 of its first
 // DPP row.  An element is a candidate when it reaches the wave threshold (an initial
-// lower bound, then the next value above the K-th slot's); the fast path is one compare of the
-// lane's chunk maximum per 8 elements, and the rare path inserts candidates one
-// at a time with a DPP row shift.  The initial bound is the K-th largest of the lanes' maxima over
-// the first chunks of all of the row's wavefronts, which is <= the K-th largest element, so no
-// top-K element is ever filtered out.
+// lower bound, then the next value above the K-th slot's); the fast path is one
+// compare of the lane's chunk maximum per 8 elements, and the rare path inserts
+// candidates one at a time with a DPP row shift.  The initial bound is the K-th
+// largest of the lanes' maxima over the first chunks of all of the row's wavefronts,
+// which is <= the K-th largest element, so no top-K element is ever filtered out.
 //
 // At the end every wavefront replaces its listed terms' fp32 exp2 values (recomputed
 // bit-identically from the exponent recorded at insertion) by fp64 values, which
 // removes the error of the largest terms from the normaliser; the waves' lists are
 // merged (each candidate, as a 64-bit key, is ranked against all of them in one pass),
 // and wave 0 combines the per-wave sums.
+//
+// A row of a few rounds may be cut into parts of a workgroup each, which the expansion
+// merges (reduce_merge.h).
 
 #include <climits>
 #include <cmath>
