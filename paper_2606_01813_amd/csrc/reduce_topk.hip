@@ -187,7 +187,7 @@ __device__ __forceinline__ float next_up(float v) {
 // Inserts an element.  A segment is read in the order of the ids, so once the list holds K elements those still
 // to come enter only above the K-th value: values equal to it (a constant row, masked logits) are no candidates.
 // (Compared with >=, each of them took a turn of the rare path's loop: 1024 rows of 151936 bf16 logits, all equal
-// or all but five masked, 7750 us, now 55 and 51, against 57 of random ones.)
+// or all but five masked, 7750 us, now 54 and 51, against 57 of random ones.)
 __device__ __forceinline__ void list_insert(WaveState& s, float v, int id, float r, int K) {
   const bool b = before(v, id, s.lv, s.lid);
   const float pv = shr1f(s.lv);
@@ -252,15 +252,15 @@ __device__ __forceinline__ void move_reference(WaveState& s, float cmax) {
 // launch pays for its length (one copy per j: 62 KB of code, the size of the instruction
 // cache).
 // Where most lanes hold candidates (values that rise along the row), the threshold first rises to a value that 16
-// of them reach; and each turn drops, in all lanes at once, the candidates that the threshold has passed.  (A row
-// of 151936 rising bf16 logits: 1858 us with a turn for each, now 59.)  Random rows pay at most 0.8% for it.
+// of them reach; and each turn drops, in all lanes at once, the candidates that the threshold has passed.  (Rows
+// of 151936 rising bf16 logits: 1858 us with a turn for each, now 66.)  A candidate that comes up when the
+// threshold has passed it changes none of the K best.
 template <int VEC>
-__device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool ok, float cmax, int base, int K,
-                                     int lane) {
+__device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool ok, float cmax,
+                                     unsigned long long cands, int base, int K, int lane) {
   static_assert(CADDTREE_MAX_K <= 16, "16 elements reach the raised threshold");
   move_reference(s, cmax);
-  const float cm1 = ok ? cmax : -INFINITY;
-  if (__builtin_expect(__popcll(__ballot(cm1 >= s.thr)) > 32, 0)) s.thr = fmaxf(s.thr, sixteenth(cm1));
+  if (__builtin_expect(__popcll(cands) > 32, 0)) s.thr = fmaxf(s.thr, sixteenth(ok ? cmax : -INFINITY));
   uint32_t cm = 0u;                            // bit j: x[j] is a candidate
 #pragma unroll
   for (int j = 0; j < VEC; ++j) cm |= (ok && x[j] >= s.thr) ? 1u << j : 0u;
@@ -270,9 +270,8 @@ __device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool o
     const int l = __builtin_ctzll(m);
     const int jl = __builtin_ctz(cm | 0x100u);   // this lane's next candidate
     const float xl = pick(x, jl);
-    const bool stays = xl >= s.thr;
-    if (__ballot(stays) >> l & 1) list_insert(s, readlane_f(xl, l), base + l * VEC + readlane_i(jl, l), s.r, K);
-    if (lane == l || !stays) cm &= cm - 1u;
+    list_insert(s, readlane_f(xl, l), base + l * VEC + readlane_i(jl, l), s.r, K);
+    if (lane == l || !(xl >= s.thr)) cm &= cm - 1u;
     m = __ballot(cm != 0u);
   }
 }
@@ -306,8 +305,9 @@ __device__ __forceinline__ void chunk(WaveState& s, const float (&x)[VEC], bool 
 #pragma unroll
   for (int j = 1; j < VEC; ++j) cmax = fmaxf(cmax, x[j]);
   const bool cand = ok && cmax >= s.thr;
-  const bool any = __ballot(cand) != 0;
-  if (__builtin_expect(any, 0)) rare<VEC>(s, x, ok, cmax, base, K, lane);
+  const unsigned long long cands = __ballot(cand);
+  const bool any = cands != 0;
+  if (__builtin_expect(any, 0)) rare<VEC>(s, x, ok, cmax, cands, base, K, lane);
   float t[VEC], p[VEC];
 #pragma unroll
   for (int j = 0; j < VEC; ++j) p[j] = t[j] = term(x[j], s.r);
