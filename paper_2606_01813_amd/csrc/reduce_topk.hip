@@ -260,7 +260,9 @@ __device__ __forceinline__ void rare(WaveState& s, const float (&x)[VEC], bool o
                                      unsigned long long cands, int base, int K, int lane) {
   static_assert(CADDTREE_MAX_K <= 16, "16 elements reach the raised threshold");
   move_reference(s, cmax);
-  if (__builtin_expect(__popcll(cands) > 32, 0)) s.thr = fmaxf(s.thr, sixteenth(ok ? cmax : -INFINITY));
+  // (a lane of NaN alone holds nothing)
+  if (__builtin_expect(__popcll(cands) > 32, 0))
+    s.thr = fmaxf(s.thr, sixteenth(ok ? fmaxf(cmax, -INFINITY) : -INFINITY));
   uint32_t cm = 0u;                            // bit j: x[j] is a candidate
 #pragma unroll
   for (int j = 0; j < VEC; ++j) cm |= (ok && x[j] >= s.thr) ? 1u << j : 0u;

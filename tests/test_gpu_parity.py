@@ -1337,3 +1337,38 @@ def test_split_rows_left_to_the_serial_form(B, cap, in_place, monkeypatch):
         assert h["n_star"][b] == n
         for k in ("token_ids", "parent", "depth", "path_prob"):
             assert np.array_equal(h[k][b, :n], h[k][0, :n]), (b, k)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("waves", [1, 2])
+def test_k1_rows_with_nan(waves, dtype, monkeypatch):
+    """NaN logits are no candidates, wherever they lie; the row's normaliser is NaN.  The last chunks of the rows
+    rise by one from lane to lane, past a first group of equal ones, and hold one value a lane: the raised threshold,
+    which 16 groups of lanes reach, must not count a group of NaN alone (lanes 3, 19, 35 and 51 of the second row),
+    or the 16th largest is lost."""
+    import torch
+    monkeypatch.setenv("CADDTREE_K1_WAVES", str(waves))
+    vec = 8 if dtype == "bf16" else 4
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    nch = 10 * waves
+    V, B, L, K = nch * 64 * vec, 2, 4, 16
+    e = np.arange(V)
+    chunk, lane = e // (64 * vec), (e // vec) % 64
+    late = chunk % 10 >= 8
+    x = np.where(e % vec == 0, np.where(late, 64.0 * (chunk % 10 - 8) + lane, -5.0), -1000.0).astype(np.float32)
+    x = np.broadcast_to(x, (B, L, V)).copy()
+    x[:, 0, 5] = np.nan
+    x[:, 1, lane % 16 == 3] = np.nan
+    x[:, 2, V // 2:] = np.nan
+    x[:, 3, lane != 15] = np.nan
+    logits = torch.from_numpy(x).to(tdt).cuda()
+    plan = make_plan(synth.get_config("c1").replace(V=V, B=B, L=L, K=K, cap=8, dtype=dtype))
+    out = plan.new_outputs(B, topk=True)
+    plan.reduce_topk(logits, out.topk_ids, out.topk_logit, out.lse, out.topk_lq)
+    torch.cuda.synchronize()
+    h = host(out)
+    xd = logits.cpu().to(torch.float64).numpy()
+    order = np.argsort(np.where(np.isnan(xd), np.inf, -xd), axis=-1, kind="stable")[..., :K]
+    assert np.array_equal(h["topk_ids"], order)
+    assert np.array_equal(h["topk_logit"].astype(np.float64), np.take_along_axis(xd, order, -1))
+    assert np.isnan(h["lse"]).all()
