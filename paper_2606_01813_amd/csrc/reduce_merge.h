@@ -39,7 +39,9 @@ __device__ __forceinline__ uint64_t order_key(float v, int id) {
   const uint32_t u = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
   return ((uint64_t)u << 32) | (uint32_t)(INT_MAX - id);
 }
-__device__ __forceinline__ int key_id(uint64_t k) { return INT_MAX - (int)(uint32_t)k; }
+// A list's empty slot as candidate i of its row's parts: below every element, and distinct, so that the ranks are.
+__device__ __forceinline__ uint64_t empty_key(int i) { return (uint64_t)(uint32_t)i; }
+__device__ __forceinline__ int key_id(uint64_t k) { return (k >> 32) != 0 ? INT_MAX - (int)(uint32_t)k : INT_MAX; }
 
 // One row's partial results, P parts (split_row_bytes(K, P) bytes a row)
 struct PartRow {
@@ -75,7 +77,7 @@ struct PartRegs {
 };
 
 // Merges a row's candidates: lane k < K gets the k-th best in v, id.  A candidate's rank among all of them is
-// its lane (real entries have distinct keys; a row holds at least K).
+// its lane (the keys are distinct).
 __device__ __forceinline__ void merge_list(const PartRegs& m, int n, int lane, float& v, int& id) {
   const uint64_t key = lane < n ? m.key : 0ull;
   const uint32_t klo = (uint32_t)key, khi = (uint32_t)(key >> 32);

@@ -518,7 +518,7 @@ reduce_topk_kernel(const T* __restrict__ logits, int64_t row_stride, int V, int 
   if (P > 1) {                             // a part's result, merged by the expansion
     const PartRow pr = part_row(parts, row, K, P);
     if (lane < K) {
-      pr.key[part * K + lane] = order_key(s.lv, s.lid);
+      pr.key[part * K + lane] = s.lid != INT_MAX ? order_key(s.lv, s.lid) : empty_key(part * K + lane);
       pr.v[part * K + lane] = s.lv;
     }
     if (lane == 0) {

@@ -1372,3 +1372,31 @@ def test_k1_rows_with_nan(waves, dtype, monkeypatch):
     assert np.array_equal(h["topk_ids"], order)
     assert np.array_equal(h["topk_logit"].astype(np.float64), np.take_along_axis(xd, order, -1))
     assert np.isnan(h["lse"]).all()
+
+
+@pytest.mark.parametrize("split", [1, 2, 4])
+@pytest.mark.parametrize("waves", [1, 4])
+def test_rows_of_fewer_numbers_than_ranks(split, waves, monkeypatch):
+    """Rows with fewer than K logits that are no NaN: the numbers in order, then empty ranks (-inf), whole or in
+    parts.  (A budget cap of 0: the normaliser is NaN, so there is no tree to build.)"""
+    import torch
+    monkeypatch.setenv("CADDTREE_K1_SPLIT", str(split))
+    monkeypatch.setenv("CADDTREE_K1_WAVES", str(waves))
+    B, L, V, K = 2, 3, 9001, 8
+    x = np.full((B, L, V), np.nan, dtype=np.float32)
+    keep = {0: [], 1: [17], 2: [9000, 3, 4500, 8000, 12]}
+    for i, ids in keep.items():
+        x[:, i, ids] = np.arange(len(ids), dtype=np.float32)
+    plan = make_plan(synth.get_config("c1").replace(V=V, B=B, L=L, K=K, cap=0, dtype="f32"))
+    out = plan.new_outputs(B, topk=True)
+    plan.build(torch.from_numpy(x).cuda(), out, workspace=plan.new_workspace(B))
+    torch.cuda.synchronize()
+    h = host(out)
+    for i, ids in keep.items():
+        n = len(ids)
+        for b in range(B):
+            assert h["topk_ids"][b, i, :n].tolist() == ids[::-1]
+            assert h["topk_logit"][b, i, :n].tolist() == list(range(n))[::-1]
+            assert (h["topk_logit"][b, i, n:] == -np.inf).all()
+            assert (h["topk_ids"][b, i, n:] == 2 ** 31 - 1).all()
+    assert np.isnan(h["lse"]).all() and (h["n_star"] == 0).all()
